@@ -111,7 +111,8 @@ typedef struct {
                                 iteration ran since the state was set */
     double objective;        /* energy objective of z, as twa_get_quality */
     double min_clearance;    /* smallest clearance of z, as twa_get_quality */
-    long long graph_iterations; /* iterations run so far from replayed HIP graphs */
+    long long graph_iterations; /* iterations run so far without launches of their own: replayed from
+                                   HIP graphs, or inside a group's launch */
     long long tape_checkpoints; /* checkpoints of the current run on the forward tape
                                    (TWA_F_TAPE: made by the first twa_backward, it records
                                    from the next start of a run; see twa_backward) */
@@ -196,8 +197,10 @@ twa_status twa_set_schedule(twa_solver *s, float rho0_init, int n_warm);
  * the steady rho0 are replayed from HIP graphs of 32, 16, ..., 1 iterations
  * (captured together the first time, so any k replays); an instance of at
  * most 256 collision + wall factors (or 512 collision factors and no walls)
- * runs them in one persistent single-workgroup launch instead (bitwise the
- * same iterations). */
+ * runs them in one persistent single-workgroup launch instead, and a
+ * mid-sized one (up to 700,000 factors whose break-points fit a workgroup's
+ * LDS) in one launch of a group of resident workgroups (bitwise the same
+ * iterations). */
 twa_status twa_iterate(twa_solver *s, int k);
 
 /* Iterate until the plan is collision-free: up to max_iter >= 0 iterations

@@ -159,7 +159,7 @@ struct twa_solver {
     static constexpr int kGraphSizes = 6;
     hipGraphExec_t graphs[kGraphSizes] = {};
     bool graph_failed = false;
-    long long graph_iters = 0;  // iterations run from graph replays
+    long long graph_iters = 0;  // iterations run from graph replays or in group launches
     hipStream_t own_stream = nullptr; // made at create when the caller passes the null stream
     bool no_capture = false;          // inside a call that allocates nothing: capture no new graph
     std::vector<float> h_radii, h_walls; // host copies for validating new end points
@@ -171,6 +171,16 @@ struct twa_solver {
     // (a device copy of the parameters and its one-bin layout)
     twa_rt::Params *tiny_params = nullptr;
     int *tiny_bins = nullptr;
+    // mid-sized instances: the group of resident workgroups that runs their
+    // iterations (group.h): its shared words, the three rotating buffers of
+    // consensus sums and counts, the per-segment factors' x and whether they
+    // sent rho0, and its shares (0: plain launches)
+    void *group_ctl = nullptr;
+    unsigned long long *group_acc = nullptr;
+    int *group_cnt = nullptr;
+    float *group_xe = nullptr;
+    unsigned char *group_sent = nullptr;
+    int group_want = 0;
     // TWA_F_TAPE: the state the differentiated run starts from (canonical
     // layouts), saved by create / set_init / set_state
     float *origin_z = nullptr, *origin_u = nullptr;

@@ -1636,6 +1636,9 @@ __global__ __launch_bounds__(BLOCK) void k_tiny(const Params *src, TinyLds L, in
     }
 }
 
+// ------------------------------------------------------------------ group of resident workgroups
+#include "group.h"
+
 __global__ void k_reset_counters(Params P) {
     if (threadIdx.x < 4) P.counters[threadIdx.x] = 0;
     if (threadIdx.x < kShards) P.qcnt[threadIdx.x * kQueueStride] = 0;
@@ -2087,6 +2090,125 @@ twa_status iterate_tiny(twa_solver *s, int k) {
     return TWA_OK;
 }
 
+constexpr unsigned kGroupLdsMax = 158u << 10; // of a compute unit's 160 KiB, less the kernel's own words
+
+// LDS layout of a group of `want` shares; false when it does not fit.
+bool group_layout(const twa_solver *s, int want, GroupLds *L, unsigned *bytes) {
+    const Params &P = s->P;
+    const long long items = P.cps * ((P.eta + kGroupCpw - 1) / kGroupCpw), units = (P.Fw + 31) / 32;
+    L->items = (int)((items + want - 1) / want);
+    L->walls32 = (int)((units + want - 1) / want);
+    long long off = 0;
+    auto take = [&](long long n) {
+        const long long at = off;
+        off += (n + 15) & ~15LL;
+        return (unsigned)at;
+    };
+    L->zc = take(16 * P.N);
+    L->zp = take(P.dense ? 16 * P.N : 0);
+    L->rad = take(4LL * P.p);
+    L->item = take(8LL * L->items);
+    L->word = take(8LL * L->items * kGroupCpw);
+    L->wbit = take(4LL * L->walls32);
+    L->q = take(P.Fc > 0 ? 4LL * kGroupQueue : 0);
+    L->qw = take(P.Fw > 0 ? 4LL * kGroupWallQueue : 0);
+    L->total = (unsigned)off;
+    *bytes = (unsigned)off;
+    return off <= (long long)kGroupLdsMax;
+}
+
+template <int D, bool DENSE>
+twa_status group_attr(twa_solver *s) {
+    HIP_TRY(s, hipFuncSetAttribute(reinterpret_cast<const void *>(k_group<D, DENSE>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGroupLdsMax));
+    return TWA_OK;
+}
+
+// Mid-sized instances (beyond the one-workgroup path, up to this many
+// collision + wall factors, node records within a workgroup's LDS) run their
+// steady iterations in a group of resident workgroups.  us per iteration,
+// three launches against the group: 3k factors 18.5 / 8.6, 16k 19.3 / 9.0, 40k
+// 19.5 / 10.4, 261k 20.1 / 14.7, 653k (walls) 23.3 / 20.8; ADMM at 3k 21.1 /
+// 10.4.  Past that the walk of 128 members takes as long as the launches save.
+constexpr long long kGroupFactors = 700000;
+
+// Choose the group of a mid-sized instance and allocate what its launches
+// share; leaves s->group_want 0 where the plain launches are kept.
+twa_status prepare_group(twa_solver *s) {
+    const Params &P = s->P;
+    if (P.Fc + P.Fw > kGroupFactors) return TWA_OK;
+    // Shares: a member's walk takes about 1 us per 2,000 factors, a barrier
+    // of 32 / 64 / 128 members 0.9 / 1.4 / 2.1 us.  us per iteration with 32,
+    // 64, 128 shares: 40k factors 10.4, 10.6, 11.7; 110k (walls) 16.4, 14.0,
+    // 14.3; 261k 18.7, 15.5, 14.7; 653k (walls) 36, 25, 20.8.
+    int want = 32;
+    while (want < 128 && P.Fc + P.Fw >= 2250LL * want) want *= 2;
+    GroupLds L;
+    unsigned bytes;
+    if (!group_layout(s, want, &L, &bytes)) return TWA_OK;
+    GroupCtl *ctl;
+    TRY(dev_alloc(s, &ctl, 1));
+    TRY(dev_alloc(s, &s->group_acc, (size_t)3 * s->dim * P.N));
+    TRY(dev_alloc(s, &s->group_cnt, (size_t)3 * P.N));
+    TRY(dev_alloc(s, &s->group_xe, (size_t)(P.Fe * 2 + (P.vo ? P.p : 0)) * s->dim));
+    TRY(dev_alloc(s, &s->group_sent, (size_t)P.Fe));
+    HIP_TRY(s, hipMemsetAsync(ctl, 0, sizeof(GroupCtl), s->stream));
+    HIP_TRY(s, hipMemsetAsync(s->group_acc, 0, sizeof(unsigned long long) * 3 * s->dim * P.N, s->stream));
+    HIP_TRY(s, hipMemsetAsync(s->group_cnt, 0, sizeof(int) * 3 * P.N, s->stream));
+    if (s->dim == 2) TRY(P.dense ? (group_attr<2, true>(s)) : (group_attr<2, false>(s)));
+    else TRY(P.dense ? (group_attr<3, true>(s)) : (group_attr<3, false>(s)));
+    s->group_ctl = ctl;
+    s->group_want = want;
+    return TWA_OK;
+}
+
+constexpr int kGroupChunk = 1024; // iterations per launch at most
+
+// whether a wait inside a group ever ran out (copied behind the stream's work)
+twa_status group_stuck(twa_solver *s, unsigned *stuck) {
+    if (s->group_ctl)
+        HIP_TRY(s, hipMemcpyAsync(stuck, &static_cast<GroupCtl *>(s->group_ctl)->stuck, sizeof(unsigned),
+                                  hipMemcpyDeviceToHost, s->stream));
+    return TWA_OK;
+}
+
+// k iterations of a mid-sized instance at the steady rho0, a u update
+// pending (bitwise the plain iterations).
+twa_status iterate_group(twa_solver *s, int k) {
+    GroupArgs A;
+    unsigned bytes;
+    A.ctl = static_cast<GroupCtl *>(s->group_ctl);
+    A.acc = s->group_acc;
+    A.cnt = s->group_cnt;
+    A.xe = s->group_xe;
+    A.sent = s->group_sent;
+    A.want = s->group_want;
+    // workgroups go to the 8 XCDs in turn: every 256 / want-th one keeps the
+    // members on as few XCDs as their number allows (speed only)
+    A.stride = 256 / A.want;
+    (void)group_layout(s, A.want, &A.L, &bytes);
+    Params P = s->P;
+    P.rho = P.rho_prev = s->rho0;
+    P.step = P.step_prev = s->alpha / s->rho0;
+    const dim3 grid((unsigned)(A.want * A.stride)), block(kGroupBlock);
+    while (k > 0) {
+        A.K = std::min(k, kGroupChunk);
+        hipLaunchKernelGGL(k_group_arm, dim3(1), dim3(64), 0, s->stream, A.ctl);
+        if (s->dim == 2) {
+            if (P.dense) hipLaunchKernelGGL((k_group<2, true>), grid, block, bytes, s->stream, P, A);
+            else hipLaunchKernelGGL((k_group<2, false>), grid, block, bytes, s->stream, P, A);
+        } else {
+            if (P.dense) hipLaunchKernelGGL((k_group<3, true>), grid, block, bytes, s->stream, P, A);
+            else hipLaunchKernelGGL((k_group<3, false>), grid, block, bytes, s->stream, P, A);
+        }
+        HIP_TRY(s, hipGetLastError());
+        s->iter += A.K;
+        s->graph_iters += A.K;
+        k -= A.K;
+    }
+    return TWA_OK;
+}
+
 // Run k iterations; graph replays where possible.  timed: the last
 // kTimedTail iterations are launched on their own, with events.
 twa_status iterate_core(twa_solver *s, int k, bool timed) {
@@ -2099,6 +2221,11 @@ twa_status iterate_core(twa_solver *s, int k, bool timed) {
     }
     while (k > 0) {
         const bool steady = s->pending && s->iter - 1 >= s->n_warm && !s->dbg_rho && !s->adj_pool;
+        if (steady && k - tail > 0 && s->group_want > 0) {
+            TRY(iterate_group(s, k - tail));
+            k = tail;
+            continue;
+        }
         // (a call that must not allocate replays graphs already captured but
         // captures none: instantiating a graph allocates)
         if (steady && k - tail > 0 && (s->graphs[0] || !s->no_capture) && capture_graphs(s)) {
@@ -2659,6 +2786,9 @@ twa_status twa_create(int p, int eta, int dim, const float *radii, const float *
     if (tiny(s)) {
         const twa_status st = prepare_tiny(s);
         if (st != TWA_OK) return bail(st);
+    } else {
+        const twa_status st = prepare_group(s);
+        if (st != TWA_OK) return bail(st);
     }
     if ((flags & TWA_F_TAPE) && twa_rt::tape_setup(s) != TWA_OK) return bail(TWA_E_DEVICE);
     if (hipStreamSynchronize(s->stream) != hipSuccess) return bail(TWA_E_DEVICE);
@@ -2852,8 +2982,11 @@ twa_status twa_get_stats(twa_solver *s, twa_stats *out) {
     HIP_TRY(s, hipMemcpyAsync(h, s->stats_dev, sizeof(int) * 3, hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(s, hipMemcpyAsync(&r, s->resid_dev, sizeof(unsigned), hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(s, hipMemcpyAsync(&overflow, s->P.counters + 5, sizeof(int), hipMemcpyDeviceToHost, s->stream));
+    unsigned stuck = 0;
+    TRY(group_stuck(s, &stuck));
     double obj = 0, clr = 0;
     TRY(twa_get_quality(s, &obj, &clr, nullptr)); // synchronises
+    if (stuck) return fail(s, TWA_E_DEVICE, "a group of workgroups gave up waiting for a member");
     out->iter = s->iter;
     out->active_coll = h[0];
     out->active_wall = h[1];
@@ -2923,7 +3056,10 @@ twa_status twa_check_finite(twa_solver *s) {
     int bad = 0, overflow = 0;
     HIP_TRY(s, hipMemcpyAsync(&bad, s->bad_dev, sizeof(int), hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(s, hipMemcpyAsync(&overflow, s->P.counters + 5, sizeof(int), hipMemcpyDeviceToHost, s->stream));
+    unsigned stuck = 0;
+    TRY(group_stuck(s, &stuck));
     HIP_TRY(s, hipStreamSynchronize(s->stream));
+    if (stuck) return fail(s, TWA_E_DEVICE, "a group of workgroups gave up waiting for a member");
     if (bad) return fail(s, TWA_E_NUMERIC, "non-finite value in z or u");
     if (overflow) return fail(s, TWA_E_NUMERIC, "consensus sum beyond its fixed-point range (diverging iterates)");
     return TWA_OK;
