@@ -135,12 +135,6 @@ __device__ __forceinline__ void group_barrier(GroupCtl *c, unsigned size, unsign
     __syncthreads();
 }
 
-// agent j's position relative to agent i's
-template <int D>
-__device__ __forceinline__ f3 relative(float4 ri, float4 rj) {
-    return f3{rj.x - ri.x, rj.y - ri.y, D == 3 ? rj.z - ri.z : 0.f};
-}
-
 // A share of the factors: items sh, sh + want, ... of the collision walk;
 // ranges of 32-factor wall units and of energy and fixed factors.
 struct GroupShare {
@@ -389,27 +383,24 @@ __device__ __forceinline__ void group_run(Params P, const GroupArgs &A, char *ld
                     const int j0 = (int)__builtin_amdgcn_readfirstlane((int)(pk & 0xffffffull));
                     const int ns = min(CPW, P.eta - s0);
                     const int j = j0 + lane;
-                    const bool valid = j < p;
-                    const int jj = valid ? j : j0;
+                    const bool valid = j > i && j < p;
+                    const int jj = min(j, p - 1);
+                    const unsigned long long act = __builtin_amdgcn_ballot_w64(valid);
                     const float R = rad[i] + rad[jj];
                     const float4 *ci = zc + s0 * p + i, *cj = zc + s0 * p + jj;
                     unsigned long long queue[CPW], prev[CPW]; // lanes to queue, and those active last iteration
                     if constexpr (!DENSE) {
                         float4 ri[CPW + 1], rj[CPW + 1];
 #pragma unroll
-                        for (int k = 0; k <= CPW; ++k)
-                            if (k <= ns) ri[k] = ci[k * p], rj[k] = cj[k * p];
+                        for (int k = 0; k <= CPW; ++k) ri[k] = ci[min(k, ns) * p], rj[k] = cj[min(k, ns) * p];
+                        // an inactive factor's u is zero, so its n is z
+                        cpa_masks<D, CPW>(ri, rj, R * R, queue);
 #pragma unroll
                         for (int k = 0; k < CPW; ++k) {
-                            queue[k] = prev[k] = 0ull;
-                            if (k < ns) {
-                                prev[k] = word[l * CPW + k];
-                                // an inactive factor's u is zero, so its n is z
-                                const f3 d0 = relative<D>(ri[k], rj[k]), d1 = relative<D>(ri[k + 1], rj[k + 1]);
-                                queue[k] = __ballot(valid && cpa_below(d0, d1, R * R)) | prev[k];
-                                if (lane == 0) word[l * CPW + k] = 0ull;
-                            }
+                            prev[k] = uniform64(word[l * CPW + k]);
+                            queue[k] = k < ns ? (queue[k] & act) | prev[k] : 0ull;
                         }
+                        if (lane < CPW) word[l * CPW + lane] = 0ull;
                     } else {
                         const float4 *pi = zp + s0 * p + i, *pj = zp + s0 * p + jj;
                         const unsigned fr = (unsigned)((long long)i * (2 * p - i - 1) / 2 + (j - i - 1));

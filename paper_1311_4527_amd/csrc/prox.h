@@ -99,6 +99,35 @@ TWA_HD float segseg_sq(f2 p0, f2 p1, f2 q0, f2 q1) {
     return m;
 }
 
+// Whether segments [p0,p1] and [q0,q1] come closer than r: the value of
+// segseg_sq(p0, p1, q0, q1) < r * r.  Most pairs are far apart, and say so
+// without the four point distances (a division each): both ends p beyond the
+// line of q on one side, or both past the same end of q, by more than r plus a
+// margin.  With S the largest coordinate and u = 2^-24, segseg_sq's rounding
+// moves a distance by at most 22 u S and the bounds below are off by at most
+// 16 u S; the margin is 168 u S, so a pair called far has a computed distance
+// of at least r.  (Crossing is decided first, by the same signs.)
+TWA_HD bool segseg_below(f2 p0, f2 p1, f2 q0, f2 q1, float r) {
+    const float o1 = orient(p0, p1, q0), o2 = orient(p0, p1, q1);
+    const float o3 = orient(q0, q1, p0), o4 = orient(q0, q1, p1);
+    if (((o1 > 0.f && o2 < 0.f) || (o1 < 0.f && o2 > 0.f)) && ((o3 > 0.f && o4 < 0.f) || (o3 < 0.f && o4 > 0.f)))
+        return 0.f < r * r;
+    const f2 d = sub(q1, q0);
+    const float L2 = dot(d, d);
+    const float S = fmaxf(fmaxf(fmaxf(fabsf(p0.x), fabsf(p0.y)), fmaxf(fabsf(p1.x), fabsf(p1.y))),
+                          fmaxf(fmaxf(fabsf(q0.x), fabsf(q0.y)), fmaxf(fabsf(q1.x), fabsf(q1.y))));
+    const float reach = sqrtf(L2) * (r + 1e-5f * S);
+    const float b0 = dot(sub(p0, q0), d), b1 = dot(sub(p1, q0), d);
+    const bool far = fminf(o3, o4) > reach || fmaxf(o3, o4) < -reach || fmaxf(b0, b1) < -reach ||
+                     fminf(b0, b1) > L2 + reach;
+    if (far && L2 > 1e-30f) return false;
+    float m = point_seg_sq(p0, q0, q1);
+    m = fminf(m, point_seg_sq(p1, q0, q1));
+    m = fminf(m, point_seg_sq(q0, p0, p1));
+    m = fminf(m, point_seg_sq(q1, p0, p1));
+    return m < r * r;
+}
+
 // ---------------------------------------------------------------------------
 // Energy minimiser, App. E (eq. energy_minimizer_output) with the limits of
 // infinite weights and of two equal weights tending to zero.

@@ -103,6 +103,10 @@ constexpr int kBlock = 256;
 // the appends of the whole grid do not serialise on one address.  A shard
 // holds every factor its waves could append (no overflow is possible).
 constexpr int kShards = 32;
+// Rows of the pair triangle that a wave of the activity-bit stream takes
+// together (coll_rows_bits); 1024 / 2048 agents and 32 walls: 2 rows 14.8 / 45.6
+// us, 4 rows 14.0 / 40.7, 6 rows 14.5 / 39.3.
+constexpr int kRows = 4;
 constexpr int kQueueStride = 64;
 
 enum Mode : int { M_FIRST = 0, M_FUSED = 1, M_FINAL = 2 };
@@ -404,9 +408,198 @@ __device__ __forceinline__ bool coll_factor(const Params &P, long long f, float 
     return push_prev || push_new;
 }
 
-// Collision column col: the pairs (i, j0 + lane) of one chunk of row i of
-// the pair triangle (rows are cut into chunks of 64, so i is the same for
-// the whole wave), over the break-point intervals s0 <= s < s1 <= s0 + CPW.
+// agent j's position relative to agent i's
+template <int D>
+__device__ __forceinline__ f3 relative(float4 ri, float4 rj) {
+    return f3{rj.x - ri.x, rj.y - ri.y, D == 3 ? rj.z - ri.z : 0.f};
+}
+
+// dot3 and |cross|^2 as cpa_below rounds them, without the products with a
+// planar instance's zero components (which change no comparison)
+template <int D>
+__device__ __forceinline__ float dot_as3(f3 a, f3 b) {
+    const float t = __builtin_fmaf(a.x, b.x, a.y * b.y);
+    return D == 3 ? __builtin_fmaf(a.z, b.z, t) : t;
+}
+template <int D>
+__device__ __forceinline__ float cross_sq(f3 a, f3 b) {
+    const float cz = __builtin_fmaf(a.x, b.y, -(a.y * b.x));
+    if (D == 2) return cz * cz;
+    const float cx = __builtin_fmaf(a.y, b.z, -(a.z * b.y)), cy = __builtin_fmaf(a.z, b.x, -(a.x * b.z));
+    return __builtin_fmaf(cz, cz, __builtin_fmaf(cx, cx, cy * cy));
+}
+
+// cpa_below over NS consecutive intervals, on wave masks: act[k] holds the
+// lanes whose relative motion d[k] -> d[k + 1] comes closer than sqrt(R2).
+// The three cases are combined in scalar registers, a break-point's distance
+// test serves both its intervals, and no lane branches (20 vector
+// instructions per planar interval; cpa_below itself compiles to 50 and a
+// branch here).
+template <int D, int NS>
+__device__ __forceinline__ void cpa_masks(const float4 *ri, const float4 *rj, float R2, unsigned long long *act) {
+    f3 d0 = relative<D>(ri[0], rj[0]);
+    unsigned long long in0 = __builtin_amdgcn_ballot_w64(dot_as3<D>(d0, d0) < R2);
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        const f3 d1 = relative<D>(ri[k + 1], rj[k + 1]), e = sub3(d1, d0);
+        const unsigned long long in1 = __builtin_amdgcn_ballot_w64(dot_as3<D>(d1, d1) < R2);
+        const unsigned long long at0 = __builtin_amdgcn_ballot_w64(dot_as3<D>(d0, e) >= 0.f);
+        const unsigned long long at1 = __builtin_amdgcn_ballot_w64(dot_as3<D>(d1, e) <= 0.f);
+        const unsigned long long inm = __builtin_amdgcn_ballot_w64(cross_sq<D>(d0, e) < R2 * dot_as3<D>(e, e));
+        act[k] = (at0 & in0) | (~at0 & ((at1 & in1) | (~at1 & inm)));
+        d0 = d1;
+        in0 = in1;
+    }
+}
+
+// a 64-bit value that is the same on every lane, in scalar registers
+__device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {
+    const unsigned lo = __builtin_amdgcn_readfirstlane((int)(unsigned)v);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32));
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+// chunk J of row i is rowchunk(p, i) + J within a break-point interval: row i
+// holds the chunks (i + 1) >> 6 to (p - 1) >> 6, after those of the rows
+// before it
+__host__ __device__ __forceinline__ int rowchunk(int p, int i) {
+    const int q = i >> 6;
+    return i * (((p - 1) >> 6) + 1) - (32 * q * (q - 1) + q * (i - 64 * q + 1)) - ((i + 1) >> 6);
+}
+
+__device__ __forceinline__ float lane_value(float v, int l) {
+    return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(v), l));
+}
+__device__ __forceinline__ unsigned long long lane_value(unsigned long long v, int l) {
+    return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), l) << 32) |
+           (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, l);
+}
+
+// cpa_masks of one row: agent i's records and radius are lanes r (NS + 1) ...
+// of `mine` and lane r of `radi`.
+template <int D, int NS>
+__device__ __forceinline__ void row_masks(float4 mine, float radi, float rjj, const float4 *rj, int r,
+                                          unsigned long long *act) {
+    const float R = lane_value(radi, r) + rjj;
+    float4 ri[NS + 1];
+#pragma unroll
+    for (int k = 0; k <= NS; ++k)
+        ri[k] = make_float4(lane_value(mine.x, r * (NS + 1) + k), lane_value(mine.y, r * (NS + 1) + k),
+                            D == 3 ? lane_value(mine.z, r * (NS + 1) + k) : 0.f, 0.f);
+    cpa_masks<D, NS>(ri, rj, R * R, act);
+}
+
+// Collision factors (i, 64 J + lane) of up to ROWS rows i0 <= i < i1 in the
+// activity-bit form after the first iteration, ns <= NS intervals from s0.  A
+// factor that was inactive has u = 0, so its n is z and the test needs the
+// agents' relative positions only; what is queued, and why, are wave masks:
+// the test's, and the chunk's activity word.  Break-points past s0 + ns are
+// read as that one.  The appends of a row share one atomic.
+//
+// The rows share one load of agent j's records; agent i's, the activity words
+// and the radii of all rows come with one vector load each, a lane per value,
+// and are handed out by lane reads.  (As scalar loads, 19 a row and nearly all
+// of them missing that cache, they bound the kernel.)  The first pass over
+// the rows only finds those with anything to queue, so that it holds few
+// scalar registers; they are then tested again.  33.5 M tests (2048 agents, 16
+// intervals, no walls): one lane per test with its own branches 66 us, masks
+// 48.5, with rows sharing loads 44, without scalar loads 37.6, in two passes
+// 36.2 (8.4 M tests of 1024 agents: 19, 14.8, 15, 13.7, 12.8).  Its vector
+// instructions take 21 us to issue.
+template <int D, int NS, int ROWS>
+__device__ __forceinline__ void coll_rows_bits(const Params &P, const Rec &Z, int i0, int i1, int J, int s0, int ns,
+                                               int lane, bool clear_bits, unsigned *qs, int *qlen) {
+    static_assert(ROWS * (NS + 1) <= 64, "a lane per record of the rows");
+    const int p = P.p, j = 64 * J + lane, cps = (int)P.cps;
+    const int jj = min(j, p - 1); // in-bounds address for idle lanes
+    const float4 *c = Z.cur + s0 * p;
+    // lane r (NS + 1) + k: agent i0 + r at break-point s0 + k
+    const int rr = min(lane / (NS + 1), ROWS - 1), rk = lane - rr * (NS + 1);
+    const float4 mine = c[min(rk, ns) * p + min(i0 + rr, p - 1)];
+    const float radi = P.radii[min(i0 + lane, p - 1)], rjj = P.radii[jj];
+    // lane r NS + k: the activity word of (i0 + r, J) in interval s0 + k
+    const int wr = min(lane / NS, ROWS - 1), wk = lane - wr * NS, wi = i0 + wr;
+    unsigned long long *words = P.bits_coll + (long long)s0 * cps;
+    const int wat = wk * cps + rowchunk(p, wi) + J;
+    const bool has = lane < ROWS * NS && wk < ns && wi < i1 && J >= ((wi + 1) >> 6);
+    const unsigned long long mword = has ? words[wat] : 0ull;
+    float4 rj[NS + 1];
+#pragma unroll
+    for (int k = 0; k <= NS; ++k) rj[k] = c[min(k, ns) * p + jj];
+    // rows that had an active factor, then those with a close pair
+    const unsigned long long was = __builtin_amdgcn_ballot_w64(mword != 0ull);
+    if (clear_bits && mword != 0ull) words[wat] = 0ull;
+    const unsigned long long tail = p - 64 * J < 64 ? (1ull << (p - 64 * J)) - 1ull : ~0ull;
+    const int rows = min(i1 - i0, ROWS);
+    unsigned busy = 0u;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const int i = i0 + r;
+        if (r < rows && J >= ((i + 1) >> 6)) {
+            unsigned long long act[NS];
+            row_masks<D, NS>(mine, radi, rjj, rj, r, act);
+            unsigned long long some = 0ull;
+#pragma unroll
+            for (int k = 0; k < NS; ++k) some |= k < ns ? act[k] : 0ull;
+            const unsigned long long valid = tail & (i >= 64 * J ? ~0ull << (i - 64 * J + 1) : ~0ull); // i < j < p
+            const unsigned long long mineword = was >> (r * NS) & ((1ull << NS) - 1ull);
+            if ((some & valid) | mineword) busy |= 1u << r;
+        }
+    }
+    if (P.dbg_rho) busy = (1u << rows) - 1u; // (a capture writes every factor)
+    if (busy == 0u) return; // nothing was active and nothing is queued: the common case
+    const unsigned P2 = (unsigned)P.P2;
+    const unsigned long long me = 1ull << lane;
+#pragma unroll 1
+    for (int r = 0; r < rows; ++r) {
+        const int i = i0 + r;
+        if (!((busy >> r) & 1u) || J < ((i + 1) >> 6)) continue;
+        unsigned long long queue[NS];
+        row_masks<D, NS>(mine, radi, rjj, rj, r, queue);
+        const unsigned long long valid = tail & (i >= 64 * J ? ~0ull << (i - 64 * J + 1) : ~0ull);
+        unsigned long long word[NS];
+        int n = 0;
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+            word[k] = lane_value(mword, r * NS + k);
+            queue[k] = k < ns ? (queue[k] & valid) | word[k] : 0ull;
+            n += __popcll(queue[k]);
+        }
+        // canonical index of (s, i, j): s p(p-1)/2 + fr (31 bits)
+        const unsigned fr = (unsigned)((long long)i * (2 * p - i - 1) / 2 + (j - i - 1));
+        if (P.dbg_rho) {
+            // capture of an iteration: the factors that stay inactive (x = n = z)
+            for (int k = 0; k < ns; ++k) {
+                unsigned long long qk = 0ull;
+#pragma unroll
+                for (int m = 0; m < NS; ++m) qk = m == k ? queue[m] : qk;
+                if (!(valid & ~qk & me)) continue;
+                const long long f = (s0 + k) * P2 + fr, e0 = P.e_coll + 4 * f;
+                if (P.dbg_x)
+                    for (int e = 0; e < 4; ++e) {
+                        float zz[3];
+                        node_xyz(c[(k + (e & 1)) * p + (e < 2 ? i : jj)], zz, D);
+                        for (int q = 0; q < D; ++q) P.dbg_x[(e0 + e) * D + q] = zz[q];
+                    }
+                P.dbg_rho[P.f_coll + f] = W_ZERO;
+            }
+        }
+        if (n == 0) continue;
+        int base = 0;
+        if (lane == 0) base = atomicAdd(qlen, n);
+        base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+            if (queue[k] & me)
+                qs[base + __popcll(queue[k] & (me - 1ull))] = ((s0 + k) * P2 + fr) | ((word[k] & me) ? kPrev : 0u);
+            base += __popcll(queue[k]);
+        }
+    }
+}
+
+// Collision column col: the pairs (i, j0 + lane), j0 a multiple of 64, of one
+// chunk of row i of the pair triangle (so i is the same for the whole wave;
+// lanes with j <= i are idle), over the break-point intervals s0 <= s < s1 <= s0 + CPW.
 // Every load of the column (node records of break-points s0..s1, agent i's
 // through the scalar cache when SCALAR_I, i.e. when Z points to global
 // memory; the chunks' activity words; u where it is read) is issued before
@@ -423,10 +616,14 @@ __device__ __forceinline__ void coll_column(const Params &P, const Rec &Z, int c
     const int cu = __builtin_amdgcn_readfirstlane(col);
     const unsigned long long pk = load_uniform(P.chunk_coll, cu);
     const int i = (int)(pk >> 24), j0 = (int)(pk & 0xffffffull);
+    if constexpr (!DENSE && MODE == M_FUSED) {
+        coll_rows_bits<D, CPW, 1>(P, Z, i, i + 1, j0 >> 6, s0, s1 - s0, lane, clear_bits, qs, qlen);
+        return;
+    }
     const int p = P.p;
     const int j = j0 + lane;
-    const bool valid = j < p;
-    const int jj = valid ? j : j0; // in-bounds address for idle lanes
+    const bool valid = j > i && j < p;
+    const int jj = min(j, p - 1); // in-bounds address for idle lanes
     const float R = load_uniform(P.radii, i) + P.radii[jj];
     // canonical index of (s, i, j) is s p(p-1)/2 + fr (all factor indices
     // fit in 31 bits): row i of the triangle holds the pairs (i, j > i)
@@ -524,9 +721,8 @@ __device__ __forceinline__ void coll_flat(const Params &P, const Rec &Z, long lo
             if (dense || MODE == M_FIRST) load_u_coll<D>(P, f[k], u[k]);
             if (dense && MODE != M_FIRST)
                 for (int e = 0; e < 4; ++e) rp[k][e] = Z.prev[nd[e]];
-            const int r = j[k] - i[k] - 1;
             if (!dense && MODE != M_FIRST)
-                word[k] = P.bits_coll[(long long)s[k] * P.cps + P.rowchunk[i[k]] + (r >> 6)] >> (r & 63);
+                word[k] = P.bits_coll[(long long)s[k] * P.cps + P.rowchunk[i[k]] + (j[k] >> 6)] >> (j[k] & 63);
             R[k] = P.radii[i[k]] + P.radii[j[k]];
         }
     }
@@ -589,7 +785,7 @@ __device__ __forceinline__ bool wall_test(const Params &P, const Rec &Z, const W
         u = P.u_wall[f];
         float4 za = Z.prev[a.na], zb = Z.prev[a.nb];
         f2 n0 = mk(za.x - u.x, za.y - u.y), n1 = mk(zb.x - u.z, zb.y - u.w);
-        if (segseg_sq(n0, n1, xa, xb) < r * r) {
+        if (segseg_below(n0, n1, xa, xb, r)) {
             push_prev = true;
             check_cur = false;
         } else {
@@ -609,7 +805,7 @@ __device__ __forceinline__ bool wall_test(const Params &P, const Rec &Z, const W
     if (check_cur) {
         float4 za = Z.cur[a.na], zb = Z.cur[a.nb];
         f2 n0 = mk(za.x - u.x, za.y - u.y), n1 = mk(zb.x - u.z, zb.y - u.w);
-        push_new = P.admm || segseg_sq(n0, n1, xa, xb) < r * r;
+        push_new = P.admm || segseg_below(n0, n1, xa, xb, r);
         if (!push_new && P.dbg_rho) {
             long long e0 = P.e_wall + 2 * f;
             if (P.dbg_x) {
@@ -870,8 +1066,7 @@ __device__ __forceinline__ bool coll_minimise(const Params &P, const Rec &Z, con
         }
         store_x_coll<D>(P, f, x);
         if (SET_BITS) {
-            const int r = j - i - 1;
-            atomicOr(&P.bits_coll[(long long)s * P.cps + P.rowchunk[i] + (r >> 6)], 1ull << (r & 63));
+            atomicOr(&P.bits_coll[(long long)s * P.cps + P.rowchunk[i] + (j >> 6)], 1ull << (j & 63));
         }
     } else {
         for (int q = 0; q < 4 * D; ++q) x[q] = n[q];
@@ -1061,15 +1256,36 @@ __device__ __forceinline__ void stream_block(const Params &P, long long b) {
     const bool clear_bits = MODE != M_FINAL && P.dense == 0;
     const Rec Z{P.zr_cur, P.zr_prev};
     if (b < P.nbc) {
-        // wave -> (column, block of CPW break-point intervals); consecutive
-        // waves take consecutive columns of the same intervals
+        // wave -> (column, or rows of a chunk column, block of CPW break-point
+        // intervals); consecutive waves take consecutive ones of the same
+        // intervals
         const unsigned wave = (unsigned)b * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const unsigned cps = (unsigned)P.cps;
-        const int col = (int)(wave % cps), s0 = (int)(wave / cps) * CPW;
-        const int shard = (int)(wave % kShards);
-        if (s0 < P.eta)
-            coll_column<D, MODE, CPW, DENSE, true>(P, Z, col, s0, min(s0 + CPW, P.eta), threadIdx.x & 63, clear_bits,
-                                                   P.qc + (long long)shard * P.qcap, &P.qcnt[shard * kQueueStride]);
+        const unsigned per = (unsigned)(DENSE ? P.cps : P.nwalk);
+        const int at = (int)(wave % per), s0 = (int)(wave / per) * CPW;
+        const int shard = (int)(wave % kShards), lane = threadIdx.x & 63;
+        unsigned *qs = P.qc + (long long)shard * P.qcap;
+        int *qlen = &P.qcnt[shard * kQueueStride];
+        if (s0 < P.eta) {
+            const int s1 = min(s0 + CPW, P.eta);
+            if constexpr (DENSE) {
+                coll_column<D, MODE, CPW, true, true>(P, Z, at, s0, s1, lane, clear_bits, qs, qlen);
+            } else {
+                const unsigned long long pk = load_uniform(P.walk_coll, at);
+                const int i0 = (int)(pk >> 24), J = (int)(pk & 0xffffffull), i1 = min(i0 + kRows, P.p - 1);
+                if constexpr (MODE == M_FUSED) {
+                    // (up to half the intervals left: the half-length form)
+                    if (s1 - s0 <= CPW / 2)
+                        coll_rows_bits<D, CPW / 2, kRows>(P, Z, i0, i1, J, s0, s1 - s0, lane, clear_bits, qs, qlen);
+                    else
+                        coll_rows_bits<D, CPW, kRows>(P, Z, i0, i1, J, s0, s1 - s0, lane, clear_bits, qs, qlen);
+                } else {
+                    for (int i = i0; i < i1; ++i)
+                        if (J >= ((i + 1) >> 6))
+                            coll_column<D, MODE, CPW, false, true>(P, Z, load_uniform(P.rowchunk, i) + J, s0, s1, lane,
+                                                                   clear_bits, qs, qlen);
+                }
+            }
+        }
     } else if (b < P.nbc + P.nbw) {
         long long f = (b - P.nbc) * kBlock + threadIdx.x;
         bool valid = f < P.Fw, q;
@@ -1532,8 +1748,7 @@ __device__ __forceinline__ void tiny_bits(const Params &P, const TinyOwn &o, int
         __syncthreads();
     }
     if (o.c.f >= 0 && (dense ? o.ever_c : o.act_c)) {
-        const int r = o.c.j - o.c.i - 1;
-        atomicOr(&P.bits_coll[(long long)o.c.s * P.cps + P.rowchunk[o.c.i] + (r >> 6)], 1ull << (r & 63));
+        atomicOr(&P.bits_coll[(long long)o.c.s * P.cps + P.rowchunk[o.c.i] + (o.c.j >> 6)], 1ull << (o.c.j & 63));
     }
     if (o.w.f >= 0 && (dense ? o.ever_w : o.act_w)) atomicOr(&P.bits_wall[o.w.f >> 5], 1u << (o.w.f & 31));
     __syncthreads();
@@ -1582,8 +1797,7 @@ __global__ __launch_bounds__(BLOCK) void k_tiny(const Params *src, TinyLds L, in
     const int per_c = (int)((sp.Fc + wc - 1) / wc), per_w = (int)((sp.Fw + 3) / 4);
     if (wv < wc && ln < per_c && wv * per_c + ln < sp.Fc) {
         o.c = coll_at(sp, wv * per_c + ln);
-        const int r = o.c.j - o.c.i - 1;
-        o.act_c = (sp.bits_coll[(long long)o.c.s * sp.cps + sp.rowchunk[o.c.i] + (r >> 6)] >> (r & 63)) & 1ull;
+        o.act_c = (sp.bits_coll[(long long)o.c.s * sp.cps + sp.rowchunk[o.c.i] + (o.c.j >> 6)] >> (o.c.j & 63)) & 1ull;
     } else if (wv >= 4 && ln < per_w && (wv - 4) * per_w + ln < sp.Fw) {
         const long long f = (wv - 4) * per_w + ln;
         o.w = wall_at(sp, f, sp.wbase_wall[f >> 6], (int)(f & 63));
@@ -2221,9 +2435,10 @@ twa_status iterate_core(twa_solver *s, int k, bool timed) {
     }
     while (k > 0) {
         const bool steady = s->pending && s->iter - 1 >= s->n_warm && !s->dbg_rho && !s->adj_pool;
-        if (steady && k - tail > 0 && s->group_want > 0) {
-            TRY(iterate_group(s, k - tail));
-            k = tail;
+        // (a timed call times the plain kernels, so it runs them throughout)
+        if (steady && !timed && s->group_want > 0) {
+            TRY(iterate_group(s, k));
+            k = 0;
             continue;
         }
         // (a call that must not allocate replays graphs already captured but
@@ -2642,25 +2857,43 @@ twa_status twa_create(int p, int eta, int dim, const float *radii, const float *
     P.N = (long long)p * (eta + 1);
     // break-point intervals per wave in k_stream (see k_stream)
     P.cpw = (flags & (TWA_F_DENSE | TWA_F_ADMM)) ? 4 : 8; // as k_stream<..., DENSE> (ADMM runs dense)
-    // rows of the pair triangle cut into chunks of 64: chunk (s, i, j0)
+    // rows of the pair triangle cut at the multiples of 64: chunk (s, i, J)
+    // holds the pairs (i, j) with j >> 6 == J; its index in an interval is
+    // rowchunk[i] + J
     std::vector<int> hrowchunk((size_t)p, 0);
-    for (int i = 0; i + 1 < p; ++i) hrowchunk[i + 1] = hrowchunk[i] + (p - 1 - i + 63) / 64;
-    P.cps = p > 1 ? hrowchunk[p - 1] : 0;
+    {
+        long long c = 0;
+        for (int i = 0; i + 1 < p; ++i) {
+            hrowchunk[i] = rowchunk(p, i);
+            c += ((p - 1) >> 6) - ((i + 1) >> 6) + 1;
+        }
+        P.cps = c;
+    }
     P.nch = (long long)eta * P.cps;
     P.P2 = P2;
     if (P.nch >= (1LL << 31)) {
         fail(s, TWA_E_INVALID, "too many factors for one solver");
         return bail(TWA_E_INVALID);
     }
-    // (i, j0) of each chunk of a break-point interval (the same for every s)
+    // (i, 64 J) of each chunk of a break-point interval (the same for every s)
     std::vector<unsigned long long> hchunk((size_t)std::max<long long>(1, P.cps));
     {
         long long c = 0;
         for (int i = 0; i + 1 < p; ++i)
-            for (int j0 = i + 1; j0 < p; j0 += 64, ++c)
-                hchunk[c] = ((unsigned long long)i << 24) | (unsigned long long)j0;
+            for (int J = (i + 1) >> 6; J <= (p - 1) >> 6; ++J, ++c)
+                hchunk[c] = ((unsigned long long)i << 24) | (unsigned long long)(64 * J);
     }
-    P.nbc = (P.cps * ((eta + P.cpw - 1) / P.cpw) + kBlock / 64 - 1) / (kBlock / 64);
+    // the walk of the activity-bit stream: (i0, J) for rows i0 .. i0 + kRows - 1
+    // over a chunk column J, J by J (neighbouring waves then read the same
+    // agents j)
+    std::vector<unsigned long long> hwalk;
+    for (int J = 0; J <= (p - 1) >> 6 && p > 1; ++J)
+        for (int i0 = 0; i0 + 1 < p && ((i0 + 1) >> 6) <= J; i0 += kRows)
+            hwalk.push_back(((unsigned long long)i0 << 24) | (unsigned long long)J);
+    P.nwalk = (long long)hwalk.size();
+    if (hwalk.empty()) hwalk.push_back(0ull);
+    const long long walk = (flags & (TWA_F_DENSE | TWA_F_ADMM)) ? P.cps : P.nwalk;
+    P.nbc = (walk * ((eta + P.cpw - 1) / P.cpw) + kBlock / 64 - 1) / (kBlock / 64);
     P.nbw = (Fw + kBlock - 1) / kBlock;
     P.nbe = (Fe + kBlock - 1) / kBlock;
     P.nbf = (Ff + kBlock - 1) / kBlock;
@@ -2668,8 +2901,8 @@ twa_status twa_create(int p, int eta, int dim, const float *radii, const float *
     s->nblocks_queue = 4096;
     {
         // a shard takes the appends of every kShards-th wave of the column walk
-        long long waves = P.cps * ((eta + P.cpw - 1) / P.cpw);
-        P.qcap = (waves + kShards - 1) / kShards * 64 * P.cpw;
+        long long waves = walk * ((eta + P.cpw - 1) / P.cpw);
+        P.qcap = (waves + kShards - 1) / kShards * 64 * P.cpw * (walk == P.cps ? 1 : kRows);
     }
     P.e_energy = Ff;
     P.e_coll = Ff + 2 * Fe;
@@ -2714,11 +2947,11 @@ twa_status twa_create(int p, int eta, int dim, const float *radii, const float *
         dev_alloc(s, &s->stats_dev, 4) || dev_alloc(s, &s->bad_dev, 1) || dev_alloc(s, &s->quality_dev, 3) ||
         dev_alloc(s, &s->resid_dev, 1))
         return bail(TWA_E_NOMEM);
-    unsigned long long *chunk_d;
+    unsigned long long *chunk_d, *walk_d;
     int *rowchunk_d;
-    if (dev_alloc(s, &chunk_d, hchunk.size()) || dev_alloc(s, &rowchunk_d, hrowchunk.size()))
+    if (dev_alloc(s, &chunk_d, hchunk.size()) || dev_alloc(s, &walk_d, hwalk.size()) || dev_alloc(s, &rowchunk_d, hrowchunk.size()))
         return bail(TWA_E_NOMEM);
-    P.chunk_coll = chunk_d, P.rowchunk = rowchunk_d;
+    P.chunk_coll = chunk_d, P.walk_coll = walk_d, P.rowchunk = rowchunk_d;
     if ((flags & TWA_F_TAPE) &&
         (dev_alloc(s, &s->origin_z, (size_t)P.N * dim) ||
          dev_alloc(s, &s->origin_u, (size_t)(P.e_wall + 2 * Fw) * dim) || dev_alloc(s, &s->origin_l, (size_t)P.N)))
@@ -2765,6 +2998,9 @@ twa_status twa_create(int p, int eta, int dim, const float *radii, const float *
                            s->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(chunk_d, hchunk.data(), sizeof(unsigned long long) * hchunk.size(), hipMemcpyHostToDevice,
+                           s->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(walk_d, hwalk.data(), sizeof(unsigned long long) * hwalk.size(), hipMemcpyHostToDevice,
                            s->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(rowchunk_d, hrowchunk.data(), sizeof(int) * hrowchunk.size(), hipMemcpyHostToDevice,

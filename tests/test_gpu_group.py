@@ -66,7 +66,7 @@ def test_group_equals_plain(case, flags):
     A.twa_iterate(21)         # a plain first iteration, then the group
     assert A.twa_get_stats()["graph_iterations"] == 20
     A.twa_iterate(2)          # from a settled state: one iteration in the group
-    A.twa_iterate_timed(3)    # plain iterations in between (the first of them a group of one)
+    A.twa_iterate_timed(3)    # plain iterations in between
     A.twa_iterate(34)
     _plain(B, 60)
     _same(A, B)
