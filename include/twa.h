@@ -380,14 +380,17 @@ twa_status twa_batch_create(int n, const twa_instance *inst, unsigned flags, voi
  * many lanes per workgroup and `groups` workgroups (bins; clamped to n);
  * instances are packed onto bins longest-first and each bin runs all k
  * iterations of its instances in one launch.  block 0 (groups ignored):
- * one launch per phase of an iteration (factor stream, minimisers,
- * consensus) over the blocks of every instance, so a large instance spreads
- * over many compute units.  Either way the evolution is bitwise that of the
+ * a large instance spreads over many compute units.  Without TWA_F_DENSE
+ * every instance has a group of resident workgroups sized by its factors
+ * and all k iterations run in one launch; with it, and where an instance
+ * does not fit, one launch per phase of an iteration (factor stream,
+ * minimisers, consensus) covers the blocks of every instance.  Either way the evolution is bitwise that of the
  * instances' own solvers.  Default: 256 lanes, one bin per instance. */
 twa_status twa_batch_config(twa_batch *b, int block, int groups);
 
-/* k >= 0 iterations of every instance (one launch of the persistent kernel,
- * or 3k launches in the phased form; captured in a HIP graph either way). */
+/* k >= 0 iterations of every instance: one launch of the persistent kernel;
+ * or, at block 0, one of the groups per 1024 iterations, or 3k launches of
+ * the phased form (the persistent and the phased launches as HIP graphs). */
 twa_status twa_batch_iterate(twa_batch *b, int k);
 
 /* As twa_batch_iterate; *ms = device time of the launch (synchronises). */

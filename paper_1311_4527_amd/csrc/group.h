@@ -44,18 +44,36 @@
 // barrier, so no cache is written back or invalidated.
 #pragma once
 
-constexpr int kGroupBlock = 512;                // lanes per workgroup
-constexpr int kGroupWaves = kGroupBlock / 64;
-constexpr int kGroupCpw = 2;                    // break-point intervals per item of the collision walk
-constexpr int kGroupTile = 32;                  // items of a tile (walked between two looks at the queue)
-constexpr int kGroupQueue = 2 * kGroupTile * kGroupCpw * 64;  // entries of the LDS collision queue
-constexpr int kGroupMinChunk = 16;              // least entries a wave takes from the collision queue
+constexpr int kGroupBlock = 512;      // lanes per workgroup of one instance's group
+constexpr int kGroupBatchBlock = 256; // and of a batch's groups, two or more of which share a compute unit
+constexpr int kGroupMinChunk = 16;    // least entries a wave takes from the collision queue
+
+// An item of the walk covers kGroupCpw intervals of one row's chunk, or, in a
+// batch's groups (cyclic), of kGroupSpan offsets d, 1 <= d <= p / 2, of the 64
+// agents i = 64 b + lane: pairs i, i + d (mod p), every pair once (d = p / 2 of an
+// even p from its lower half).  There lanes stay full where the rows of the pair
+// triangle leave half of them idle (68 agents: 68 chunks of 64 lanes instead of
+// 130): 256 instances 48 us per iteration instead of 69.  An instance with a
+// group to itself has few items per wave, and the walk is short beside the
+// minimisers: there the rows, whose words are the solver's own, are as fast or
+// faster (32 agents 8.3 us per iteration against 8.8, 64 agents 9.0 against 9.4).
+constexpr bool group_cyclic(int T) { return T == kGroupBatchBlock; }
+// activity words of an item
+constexpr int group_words(int T) { return (group_cyclic(T) ? kGroupSpan : 1) * kGroupCpw; }
+// items per block of intervals
+__host__ __device__ __forceinline__ int group_items(int p, int cps, int T) {
+    return group_cyclic(T) ? cyclic_items(p) : cps;
+}
+
+// entries of the LDS queues of a workgroup of T lanes
+constexpr int group_queue(int T) { return (T == kGroupBatchBlock ? 12 : 16) * T; }
+constexpr int group_wall_queue(int T) { return 2 * T; }
+
 // Queue length from which a wave sums the contributions to equal nodes before
 // the atomics: the shuffles cost a short queue 1 us, the atomics on the same
 // nodes a crowded one more (start of the 100-agent swap 22 against 17 us per
 // iteration, ADMM of 32 agents 20 against 10.4).
 constexpr int kGroupSums = 64;
-constexpr int kGroupWallQueue = 2 * kGroupBlock;
 constexpr unsigned kGroupFrozen = 0x80000000u;
 
 // Shared words of a group, each on a line of its own where it is polled.
@@ -79,6 +97,7 @@ struct GroupArgs {
     GroupCtl *ctl;
     unsigned long long *acc; // [3][dim][N]
     int *cnt;                // [3][N]
+    unsigned long long *words; // the shares' activity words, where a member runs several
     float *xe;               // [Fe][2 * dim] x of the per-segment factors, last iteration; [p][dim] of a
                              // velocity-obstacle epoch's goal factors
     unsigned char *sent;     // [Fe] whether they sent rho0
@@ -253,20 +272,20 @@ __device__ __forceinline__ void group_energy(const Params &P, const Rec &Z, cons
 // All nodes: z and <-rho of the next iteration from the sums of buffer b,
 // into the workgroup's own records (as node_update); those of [w0, w1) also
 // into the solver's.
-template <int D, bool DENSE>
+template <int D, bool DENSE, int T>
 __device__ __forceinline__ void group_nodes(const Params &P, const GroupArgs &A, int b, float4 *zc, float4 *zp, int w0,
                                             int w1) {
     constexpr int U = 4;
     const int N = (int)P.N, goal0 = P.eta * P.p;
     const unsigned long long *acc = A.acc + (long long)b * D * N;
     const int *cnt = A.cnt + (long long)b * N;
-    for (int n0 = threadIdx.x; n0 < N; n0 += U * kGroupBlock) {
+    for (int n0 = threadIdx.x; n0 < N; n0 += U * T) {
         unsigned long long a[U][D];
         int c[U];
         float4 fx[U];
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            const int nd = n0 + k * kGroupBlock;
+            const int nd = n0 + k * T;
             c[k] = 0;
             if (nd < N) {
                 if (!P.admm && (nd < P.p || (nd >= goal0 && !P.vo))) {
@@ -282,7 +301,7 @@ __device__ __forceinline__ void group_nodes(const Params &P, const GroupArgs &A,
         }
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            const int nd = n0 + k * kGroupBlock;
+            const int nd = n0 + k * T;
             if (nd < N) {
                 const float4 cur = zc[nd];
                 float4 nw = cur;
@@ -307,8 +326,108 @@ __device__ __forceinline__ void group_nodes(const Params &P, const GroupArgs &A,
     }
 }
 
+// The activity tests of one item of the walk (packed s0, b, d0 or s0, i, 64 J), its
+// factors to queue appended to q as (item and word) << 6 | lane.
+template <int D, bool DENSE, int T>
+__device__ __forceinline__ void group_item(const Params &P, const Rec &Z, unsigned long long item, int l, int lane,
+                                           const float *rad, unsigned long long *word, unsigned *q, int *len) {
+    constexpr int NS = kGroupCpw, WORDS = group_words(T);
+    static_assert(!DENSE || !group_cyclic(T), "the cyclic walk is of the activity-bit form");
+    const unsigned long long pk = uniform64(item);
+    const int s0 = (int)(pk >> 48), ns = min(NS, P.eta - s0), p = P.p;
+    // the lanes of the masks into the queue, as entries of the words from w on
+    auto append = [&](const unsigned long long (&queue)[NS], const unsigned long long (&prev)[NS], int w) {
+        const unsigned long long me = 1ull << lane;
+        int n = 0;
+#pragma unroll
+        for (int k = 0; k < NS; ++k) n += __popcll(queue[k]);
+        if (n == 0) return;
+        int base = 0;
+        if (lane == 0) base = atomicAdd(len, n);
+        base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+            if (queue[k] & me)
+                q[base + __popcll(queue[k] & (me - 1ull))] =
+                    ((prev[k] & me) ? kPrev : 0u) | (unsigned)((l * WORDS + w + k) << 6) | (unsigned)lane;
+            base += __popcll(queue[k]);
+        }
+    };
+    if constexpr (!group_cyclic(T)) {
+        const int i0 = (int)((pk >> 24) & 0xffffffull), j = (int)(pk & 0xffffffull) + lane, jj = min(j, p - 1);
+        const float4 *c = Z.cur + s0 * p;
+        const float R = rad[i0] + rad[jj];
+        const bool valid = j > i0 && j < p;
+        unsigned long long queue[NS], prev[NS];
+        if constexpr (!DENSE) {
+            // (an inactive factor's u is zero, so its n is z)
+            float4 ri[NS + 1], rj[NS + 1];
+#pragma unroll
+            for (int k = 0; k <= NS; ++k) ri[k] = c[min(k, ns) * p + i0], rj[k] = c[min(k, ns) * p + jj];
+            cpa_masks<D, NS>(ri, rj, R * R, queue);
+            const unsigned long long all = __builtin_amdgcn_ballot_w64(valid);
+#pragma unroll
+            for (int k = 0; k < NS; ++k) {
+                prev[k] = uniform64(word[l * NS + k]);
+                queue[k] = k < ns ? (queue[k] & all) | prev[k] : 0ull;
+            }
+            if (lane < NS) word[l * NS + lane] = 0ull;
+        } else {
+            const float4 *pr = Z.prev + s0 * p;
+            const unsigned fr = (unsigned)((long long)i0 * (2 * p - i0 - 1) / 2 + (j - i0 - 1)), P2 = (unsigned)P.P2;
+            float u[NS][4 * D];
+#pragma unroll
+            for (int k = 0; k < NS; ++k)
+                if (k < ns && valid) load_u_coll<D>(P, (unsigned)(s0 + k) * P2 + fr, u[k]);
+#pragma unroll
+            for (int k = 0; k < NS; ++k) {
+                bool go = false;
+                unsigned val = 0u;
+                if (k < ns && valid) {
+                    const float4 rc[4] = {c[k * p + i0], c[(k + 1) * p + i0], c[k * p + jj], c[(k + 1) * p + jj]};
+                    const float4 rp[4] = {pr[k * p + i0], pr[(k + 1) * p + i0], pr[k * p + jj], pr[(k + 1) * p + jj]};
+                    go = coll_factor<D, M_FUSED, true>(P, (unsigned)(s0 + k) * P2 + fr, R, rc, rp, u[k], 0ull, lane, &val);
+                }
+                queue[k] = __builtin_amdgcn_ballot_w64(go);
+                prev[k] = __builtin_amdgcn_ballot_w64((val & kPrev) != 0u);
+            }
+        }
+        append(queue, prev, 0);
+    } else {
+        // (the test does not depend on which of the two agents comes first)
+        const int b = (int)((pk >> 24) & 0xffffffull), d0 = (int)(pk & 0xffffffull);
+        const int i = 64 * b + lane, ii = min(i, p - 1), x0 = s0 * p;
+        const float radi = rad[ii];
+        float4 ri[NS + 1];
+#pragma unroll
+        for (int k = 0; k <= NS; ++k) ri[k] = Z.cur[x0 + min(k, ns) * p + ii];
+        const unsigned long long mword = lane < WORDS ? word[l * WORDS + lane] : 0ull;
+        if (lane < WORDS) word[l * WORDS + lane] = 0ull;
+        const unsigned long long all = p - 64 * b < 64 ? (1ull << (p - 64 * b)) - 1ull : ~0ull;
+        const int spans = min(kGroupSpan, p / 2 - d0 + 1);
+#pragma unroll 1
+        for (int r = 0; r < spans; ++r) {
+            const int d = d0 + r;
+            const int j = ii + d >= p ? ii + d - p : ii + d;
+            const float R = radi + rad[j];
+            float4 rj[NS + 1];
+#pragma unroll
+            for (int k = 0; k <= NS; ++k) rj[k] = Z.cur[x0 + min(k, ns) * p + j];
+            unsigned long long queue[NS], prev[NS];
+            cpa_masks<D, NS>(ri, rj, R * R, queue);
+            const unsigned long long valid = 2 * d == p ? all & __builtin_amdgcn_ballot_w64(i < d) : all;
+#pragma unroll
+            for (int k = 0; k < NS; ++k) {
+                prev[k] = lane_value(mword, r * NS + k);
+                queue[k] = k < ns ? (queue[k] & valid) | prev[k] : 0ull;
+            }
+            append(queue, prev, r * NS);
+        }
+    }
+}
+
 // K iterations of the instance by member `rank` of `size`.
-template <int D, bool DENSE>
+template <int D, bool DENSE, int T>
 __device__ __forceinline__ void group_run(Params P, const GroupArgs &A, char *lds, unsigned rank, unsigned size) {
     constexpr int CPW = kGroupCpw;
     // known here, so that the code below carries no trace of the rest
@@ -325,23 +444,42 @@ __device__ __forceinline__ void group_run(Params P, const GroupArgs &A, char *ld
     unsigned *wbit = reinterpret_cast<unsigned *>(lds + A.L.wbit);
     unsigned *q = reinterpret_cast<unsigned *>(lds + A.L.q), *qw = reinterpret_cast<unsigned *>(lds + A.L.qw);
     __shared__ int len[2];           // queue lengths
+    __shared__ int more;             // iteration + 1: some wave has items left
     __shared__ unsigned totals[4];   // this iteration's active and queued factors
-    for (int nd = threadIdx.x; nd < N; nd += kGroupBlock) {
+    for (int nd = threadIdx.x; nd < N; nd += T) {
         zc[nd] = P.zr_cur[nd];
         if (DENSE) zp[nd] = P.zr_prev[nd];
     }
-    for (int i = threadIdx.x; i < p; i += kGroupBlock) rad[i] = P.radii[i];
+    for (int i = threadIdx.x; i < p; i += T) rad[i] = P.radii[i];
     if (threadIdx.x < 2) len[threadIdx.x] = 0;
+    if (threadIdx.x == 0) more = 0;
     if (threadIdx.x < 4) totals[threadIdx.x] = 0u;
     P.radii = rad;
+    constexpr bool CYC = group_cyclic(T);
+    constexpr int WORDS = group_words(T);
     const int cps = (int)P.cps, nsb = (P.eta + CPW - 1) / CPW;
-    const int nitems_all = cps * nsb;
+    const int per = group_items(p, cps, T);
+    const int nitems_all = per * nsb;
     GroupShare S;
     const unsigned P2 = (unsigned)P.P2;
     const unsigned turn = agent_load(&A.ctl->turn);
     const bool many = size < (unsigned)A.want; // a member runs several shares in turn
     const int n0 = (int)((long long)N * rank / size), n1 = (int)((long long)N * (rank + 1) / size);
     const Rec Z{zc, zp};
+    const int spans = max(1, (p / 2 + kGroupSpan - 1) / kGroupSpan);
+    auto take_items = [&](int sh) {
+        for (int l = threadIdx.x; l < S.nitems; l += T) {
+            const int g = l * A.want + sh, sb = g / per, m = g - sb * per;
+            item[l] = ((unsigned long long)(sb * CPW) << 48) |
+                      (CYC ? ((unsigned long long)(m / spans) << 24) | (unsigned)(1 + m % spans * kGroupSpan)
+                           : P.chunk_coll[m]);
+        }
+    };
+    // the solver's word that word t of share sh is (rows only), -1 past the last interval
+    auto solver_word = [&](int sh, int t) {
+        const int g = t / CPW * A.want + sh, sb = g / per, sw = sb * CPW + t % CPW;
+        return sw < P.eta ? (long long)sw * cps + (g - sb * per) : -1ll;
+    };
     __syncthreads();
     for (int it = 0; it < A.K; ++it) {
         const int b = (int)((turn + (unsigned)it) % 3u), bc = (int)((turn + (unsigned)it + 1u) % 3u);
@@ -353,7 +491,7 @@ __device__ __forceinline__ void group_run(Params P, const GroupArgs &A, char *ld
             // barriers ago, and adds to it only after the next barrier
             unsigned long long *acc = A.acc + (long long)bc * D * N;
             int *cnt = A.cnt + (long long)bc * N;
-            for (int nd = n0 + (int)threadIdx.x; nd < n1; nd += kGroupBlock) {
+            for (int nd = n0 + (int)threadIdx.x; nd < n1; nd += T) {
                 for (int d = 0; d < D; ++d)
                     __hip_atomic_store(&acc[(long long)d * N + nd], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&cnt[nd], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -362,84 +500,46 @@ __device__ __forceinline__ void group_run(Params P, const GroupArgs &A, char *ld
         for (int sh = (int)rank; sh < A.want; sh += (int)size) {
             if (it == 0 || many) {
                 S.take(P, A.want, sh, nitems_all);
-                for (int l = threadIdx.x; l < S.nitems; l += kGroupBlock) {
-                    const int g = l * A.want + sh;
-                    const int sb = g / cps, col = g - sb * cps, s0 = sb * CPW;
-                    item[l] = ((unsigned long long)s0 << 48) | P.chunk_coll[col];
-                    for (int k = 0; k < CPW; ++k)
-                        word[l * CPW + k] = s0 + k < P.eta ? P.bits_coll[(long long)(s0 + k) * cps + col] : 0ull;
+                take_items(sh);
+                __syncthreads();
+                if (!CYC) {
+                    for (int t = threadIdx.x; t < S.nitems * WORDS; t += T) {
+                        const long long at = solver_word(sh, t);
+                        word[t] = at < 0 ? 0ull : P.bits_coll[at];
+                    }
+                } else if (it > 0) {
+                    const unsigned long long *own = A.words + (long long)sh * A.L.items * WORDS;
+                    for (int t = threadIdx.x; t < S.nitems * WORDS; t += T) word[t] = own[t];
+                } else {
+                    // the solver's words are cut by rows: lane by lane
+                    for (int t = wave; t < S.nitems * WORDS; t += T / 64) {
+                        const unsigned long long pk = item[t / WORDS];
+                        const int sw = (int)(pk >> 48) + t % CPW;
+                        int i, j;
+                        bool bit = false;
+                        if (sw < P.eta && group_pair(p, (int)((pk >> 24) & 0xffffffull),
+                                                     (int)(pk & 0xffffffull) + t % WORDS / CPW, lane, &i, &j))
+                            bit = (P.bits_coll[(long long)sw * cps + rowchunk(p, i) + (j >> 6)] >> (j & 63)) & 1ull;
+                        const unsigned long long w = __builtin_amdgcn_ballot_w64(bit);
+                        if (lane == 0) word[t] = w;
+                    }
                 }
-                for (int u = threadIdx.x; u < S.nu; u += kGroupBlock) wbit[u] = P.bits_wall[S.u0 + u];
+                for (int u = threadIdx.x; u < S.nu; u += T) wbit[u] = P.bits_wall[S.u0 + u];
                 __syncthreads();
             }
-            const int tiles = max(1, max((S.nitems + kGroupTile - 1) / kGroupTile,
-                                         (S.nwall + kGroupBlock - 1) / kGroupBlock));
-            for (int tile = 0; tile < tiles; ++tile) {
-                // activity tests of a tile: items by waves, one wall factor per lane
-                for (int l = tile * kGroupTile + wave; l < min((tile + 1) * kGroupTile, S.nitems); l += kGroupWaves) {
-                    const unsigned long long pk = item[l];
-                    const int s0 = (int)__builtin_amdgcn_readfirstlane((int)(pk >> 48));
-                    const int i = (int)__builtin_amdgcn_readfirstlane((int)((pk >> 24) & 0xffffffull));
-                    const int j0 = (int)__builtin_amdgcn_readfirstlane((int)(pk & 0xffffffull));
-                    const int ns = min(CPW, P.eta - s0);
-                    const int j = j0 + lane;
-                    const bool valid = j > i && j < p;
-                    const int jj = min(j, p - 1);
-                    const unsigned long long act = __builtin_amdgcn_ballot_w64(valid);
-                    const float R = rad[i] + rad[jj];
-                    const float4 *ci = zc + s0 * p + i, *cj = zc + s0 * p + jj;
-                    unsigned long long queue[CPW], prev[CPW]; // lanes to queue, and those active last iteration
-                    if constexpr (!DENSE) {
-                        float4 ri[CPW + 1], rj[CPW + 1];
-#pragma unroll
-                        for (int k = 0; k <= CPW; ++k) ri[k] = ci[min(k, ns) * p], rj[k] = cj[min(k, ns) * p];
-                        // an inactive factor's u is zero, so its n is z
-                        cpa_masks<D, CPW>(ri, rj, R * R, queue);
-#pragma unroll
-                        for (int k = 0; k < CPW; ++k) {
-                            prev[k] = uniform64(word[l * CPW + k]);
-                            queue[k] = k < ns ? (queue[k] & act) | prev[k] : 0ull;
-                        }
-                        if (lane < CPW) word[l * CPW + lane] = 0ull;
-                    } else {
-                        const float4 *pi = zp + s0 * p + i, *pj = zp + s0 * p + jj;
-                        const unsigned fr = (unsigned)((long long)i * (2 * p - i - 1) / 2 + (j - i - 1));
-                        float u[CPW][4 * D];
-#pragma unroll
-                        for (int k = 0; k < CPW; ++k)
-                            if (k < ns && valid) load_u_coll<D>(P, (unsigned)(s0 + k) * P2 + fr, u[k]);
-#pragma unroll
-                        for (int k = 0; k < CPW; ++k) {
-                            bool go = false;
-                            unsigned val = 0u;
-                            if (k < ns && valid) {
-                                const float4 rc[4] = {ci[k * p], ci[(k + 1) * p], cj[k * p], cj[(k + 1) * p]};
-                                const float4 rp[4] = {pi[k * p], pi[(k + 1) * p], pj[k * p], pj[(k + 1) * p]};
-                                go = coll_factor<D, M_FUSED, true>(P, (unsigned)(s0 + k) * P2 + fr, R, rc, rp, u[k], 0ull,
-                                                                   lane, &val);
-                            }
-                            queue[k] = __ballot(go);
-                            prev[k] = __ballot((val & kPrev) != 0u);
-                        }
-                    }
-                    int n = 0;
-#pragma unroll
-                    for (int k = 0; k < CPW; ++k) n += __popcll(queue[k]);
-                    if (n == 0) continue;
-                    int base = 0;
-                    if (lane == 0) base = atomicAdd(&len[0], n);
-                    base = __builtin_amdgcn_readfirstlane(base);
-                    const unsigned long long below = (1ull << lane) - 1ull, me = 1ull << lane;
-#pragma unroll
-                    for (int k = 0; k < CPW; ++k) {
-                        if (queue[k] & me)
-                            q[base + __popcll(queue[k] & below)] = ((prev[k] & me) ? kPrev : 0u) |
-                                                                   (unsigned)((l * CPW + k) << 6) | (unsigned)lane;
-                        base += __popcll(queue[k]);
-                    }
+            const bool fits = S.nitems * WORDS * 64 <= group_queue(T); // (nobody need look at the queue)
+            int l = wave, wt = 0; // this wave's next item, the next tile of wall factors
+            for (bool end = false; !end;) {
+                // Activity tests: items by waves, as long as the queue takes
+                // whatever the items in flight may add; one wall factor per lane.
+                constexpr int most = group_queue(T) - (T / 64) * WORDS * 64;
+                static_assert(most > 0, "an item per wave fits the queue: every round makes progress");
+                while (l < S.nitems && (fits || __hip_atomic_load(&len[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= most)) {
+                    group_item<D, DENSE, T>(P, Z, item[l], l, lane, rad, word, q, &len[0]);
+                    l += T / 64;
                 }
-                const int lw = tile * kGroupBlock + (int)threadIdx.x;
-                if (tile * kGroupBlock < S.nwall) {
+                if (wt * T < S.nwall) {
+                    const int lw = wt * T + (int)threadIdx.x;
                     bool queue = false;
                     unsigned val = 0u;
                     if (lw < S.nwall) {
@@ -451,22 +551,30 @@ __device__ __forceinline__ void group_run(Params P, const GroupArgs &A, char *ld
                     // (the 32 lanes of a word are in one wave: all have read it)
                     if (!DENSE && lw < S.nwall && (lw & 31) == 0) wbit[lw >> 5] = 0u;
                     group_push(qw, &len[1], queue, (val & kPrev) | (unsigned)lw);
+                    ++wt;
                 }
+                if (l < S.nitems && lane == 0) more = it + 1;
                 __syncthreads();
                 const int nq = len[0], nqw = len[1];
-                const bool end = tile + 1 == tiles;
+                const bool items = more == it + 1;
+                end = !items && wt * T >= S.nwall;
                 __syncthreads();
-                if (!end && nq <= kGroupQueue / 2 && nqw <= kGroupWallQueue - kGroupBlock) continue;
+                if (threadIdx.x == 0) more = 0;
+                // (room left for another round: the minimisers wait for it)
+                if (!end && nq <= most && nqw <= group_wall_queue(T) - T) {
+                    __syncthreads();
+                    continue;
+                }
                 if (threadIdx.x == 0) {
                     len[0] = len[1] = 0;
                     totals[2] += (unsigned)(nq + nqw);
                 }
                 // minimisers of the queued factors, 64 collision or 32 wall
                 // entries per wave, then the energy and fixed factors
-                const int cc = min(64, max(kGroupMinChunk, (nq + kGroupWaves - 1) / kGroupWaves));
+                const int cc = min(64, max(kGroupMinChunk, (nq + (T / 64) - 1) / (T / 64)));
                 const int kc = (nq + cc - 1) / cc, kw = (2 * nqw + 63) >> 6;
                 const int ke = end ? (S.ne + 63) >> 6 : 0, kf = end ? (S.nf + 63) >> 6 : 0;
-                for (int k = wave; k < kc + kw + ke + kf; k += kGroupWaves) {
+                for (int k = wave; k < kc + kw + ke + kf; k += (T / 64)) {
                     if (k < kc + kw) {
                         bool ac = false, aw = false;
                         float n[4 * D];
@@ -476,10 +584,12 @@ __device__ __forceinline__ void group_run(Params P, const GroupArgs &A, char *ld
                             if (lane < cc && t < nq) {
                                 const unsigned e = q[t];
                                 const int wi = (int)((e & kIdx) >> 6), ln = (int)(e & 63u);
-                                const unsigned long long pk = item[wi / CPW];
+                                const unsigned long long pk = item[wi / WORDS];
                                 CollAt c;
-                                c.s = (int)(pk >> 48) + wi % CPW, c.i = (int)((pk >> 24) & 0xffffffull);
-                                c.j = (int)(pk & 0xffffffull) + ln;
+                                c.s = (int)(pk >> 48) + wi % CPW;
+                                if (!CYC) c.i = (int)((pk >> 24) & 0xffffffull), c.j = (int)(pk & 0xffffffull) + ln;
+                                else group_pair(p, (int)((pk >> 24) & 0xffffffull),
+                                                (int)(pk & 0xffffffull) + wi % WORDS / CPW, ln, &c.i, &c.j);
                                 c.f = (long long)((unsigned)c.s * P2 +
                                                   (unsigned)((long long)c.i * (2 * p - c.i - 1) / 2 + (c.j - c.i - 1)));
                                 coll_nodes(P, c.s, c.i, c.j, c.nd);
@@ -518,13 +628,16 @@ __device__ __forceinline__ void group_run(Params P, const GroupArgs &A, char *ld
             }
             if (many || last) {
                 __syncthreads();
-                for (int l = threadIdx.x; l < S.nitems; l += kGroupBlock) {
-                    const int g = l * A.want + sh;
-                    const int sb = g / cps, col = g - sb * cps, s0 = sb * CPW;
-                    for (int k = 0; k < CPW && s0 + k < P.eta; ++k)
-                        P.bits_coll[(long long)(s0 + k) * cps + col] = word[l * CPW + k];
+                if (!CYC) {
+                    for (int t = threadIdx.x; t < S.nitems * WORDS; t += T) {
+                        const long long at = solver_word(sh, t);
+                        if (at >= 0) P.bits_coll[at] = word[t];
+                    }
+                } else if (many) {
+                    unsigned long long *own = A.words + (long long)sh * A.L.items * WORDS;
+                    for (int t = threadIdx.x; t < S.nitems * WORDS; t += T) own[t] = word[t];
                 }
-                for (int u = threadIdx.x; u < S.nu; u += kGroupBlock) P.bits_wall[S.u0 + u] = wbit[u];
+                for (int u = threadIdx.x; u < S.nu; u += T) P.bits_wall[S.u0 + u] = wbit[u];
                 __syncthreads();
             }
         }
@@ -534,8 +647,32 @@ __device__ __forceinline__ void group_run(Params P, const GroupArgs &A, char *ld
         }
         group_barrier(A.ctl, size, (unsigned)it + 1u);
         if (threadIdx.x == 0) totals[2] = 0u;
-        group_nodes<D, DENSE>(P, A, b, zc, zp, last ? n0 : 0, last ? n1 : 0);
+        group_nodes<D, DENSE, T>(P, A, b, zc, zp, last ? n0 : 0, last ? n1 : 0);
         __syncthreads();
+    }
+    if (!CYC) return;
+    // The solver's words, cut by rows: cleared, then the bits of the shares added.
+    const long long c0 = P.nch * rank / size, c1 = P.nch * (rank + 1) / size;
+    for (long long w = c0 + threadIdx.x; w < c1; w += T)
+        __hip_atomic_store(&P.bits_coll[w], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    group_barrier(A.ctl, size, (unsigned)A.K + 1u);
+    for (int sh = (int)rank; sh < A.want; sh += (int)size) {
+        if (many) {
+            S.take(P, A.want, sh, nitems_all);
+            __syncthreads();
+            take_items(sh);
+            const unsigned long long *own = A.words + (long long)sh * A.L.items * WORDS;
+            for (int t = threadIdx.x; t < S.nitems * WORDS; t += T) word[t] = own[t];
+            __syncthreads();
+        }
+        for (int t = wave; t < S.nitems * WORDS; t += T / 64) {
+            const unsigned long long w = uniform64(word[t]);
+            if (w == 0ull || !((w >> lane) & 1ull)) continue;
+            const unsigned long long pk = item[t / WORDS];
+            int i, j;
+            group_pair(p, (int)((pk >> 24) & 0xffffffull), (int)(pk & 0xffffffull) + t % WORDS / CPW, lane, &i, &j);
+            atomicOr(&P.bits_coll[((pk >> 48) + t % CPW) * cps + rowchunk(p, i) + (j >> 6)], 1ull << (j & 63));
+        }
     }
 }
 
@@ -553,15 +690,81 @@ __global__ __launch_bounds__(kGroupBlock) void k_group(Params P, GroupArgs A) {
     __syncthreads();
     if (!who[2]) return;
     const unsigned rank = __builtin_amdgcn_readfirstlane(who[0]), size = __builtin_amdgcn_readfirstlane(who[1]);
-    group_run<D, DENSE>(P, A, lds, rank, size);
+    group_run<D, DENSE, kGroupBlock>(P, A, lds, rank, size);
     if (rank == 0 && threadIdx.x == 0) {
         for (int k = 0; k < 3; ++k) P.stats[k] = (int)agent_load(&A.ctl->total[k]);
         A.ctl->turn = (A.ctl->turn + (unsigned)A.K) % 3u;
     }
 }
 
-// a group's words before a launch
-__global__ void k_group_arm(GroupCtl *c) {
-    if (threadIdx.x == 0) c->reg = c->size = c->bar = 0u;
-    if (threadIdx.x < 4) c->total[threadIdx.x] = 0u;
+// A pointer read from memory, taken as an offset from a kernel argument (base,
+// at address at), so that the compiler knows it to be global and does not use
+// generic accesses.
+template <class Q>
+__device__ __forceinline__ void in_global(Q *&p, char *base, unsigned long long at) {
+    p = reinterpret_cast<Q *>(base + (long long)((unsigned long long)p - at));
+}
+
+// A structure that the kernel does not write, at an address that is the same
+// for the whole wave, through the scalar cache: its fields are uniform values.
+template <class S>
+__device__ __forceinline__ S load_struct(const S *src) {
+    static_assert(sizeof(S) % 4 == 0, "read as 32-bit words");
+    int raw[sizeof(S) / 4];
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(S) / 4); ++k) raw[k] = load_uniform(reinterpret_cast<const int *>(src), k);
+    S out;
+    __builtin_memcpy(&out, raw, sizeof(S));
+    return out;
+}
+
+// A batch: block b belongs to the group of instance slots[b]; every instance
+// has its own parameters and group.  The phased launches wait in each of their
+// three phases for the slowest block of the whole batch and move every
+// instance's records through memory; here an instance waits for its own shares
+// alone, its records stay in LDS, and what bounds the launch is the walk's issue
+// on the compute units and the longest share.  256 instances of up to 128 agents
+// 75 -> 48 us per iteration (first iterations, which queue most factors, 390 ->
+// 570, paid back within five), 64 instances 39 -> 23, 16 of up to 60 agents 30 -> 16.
+// Three workgroups per compute unit: four spill (52 us), 384 lanes leave waves
+// idle.  The parameters come from memory by scalar loads, and the pointers among
+// them as offsets of a kernel argument: loaded as they are, every access through
+// them was a flat one and the branches on them divergent (2x).
+__global__ __launch_bounds__(kGroupBatchBlock, 3) void kp_group(const Params *insts, const GroupArgs *groups, const int *slots,
+                                                             int K, char *base, unsigned long long at) {
+    extern __shared__ __align__(16) char lds[];
+    __shared__ unsigned who[3];
+    const int inst = __builtin_amdgcn_readfirstlane(slots[blockIdx.x]);
+    if (inst < 0) return;
+    GroupArgs A = load_struct(groups + inst);
+    A.K = K;
+    in_global(A.ctl, base, at), in_global(A.acc, base, at), in_global(A.cnt, base, at), in_global(A.xe, base, at);
+    in_global(A.words, base, at), in_global(A.sent, base, at);
+    if (threadIdx.x == 0) {
+        unsigned r = 0u, m = 0u;
+        who[2] = group_join(A.ctl, A.want, &r, &m) ? 1u : 0u;
+        who[0] = r, who[1] = m;
+    }
+    __syncthreads();
+    if (!who[2]) return;
+    const unsigned rank = __builtin_amdgcn_readfirstlane(who[0]), size = __builtin_amdgcn_readfirstlane(who[1]);
+    Params P = load_struct(insts + inst);
+    in_global(P.zr_prev, base, at), in_global(P.zr_cur, base, at), in_global(P.radii, base, at), in_global(P.walls, base, at), in_global(P.C, base, at);
+    in_global(P.xfix, base, at), in_global(P.u_coll, base, at), in_global(P.u_wall, base, at), in_global(P.u_energy, base, at), in_global(P.u_fixed, base, at);
+    in_global(P.bits_coll, base, at), in_global(P.bits_wall, base, at), in_global(P.chunk_coll, base, at), in_global(P.counters, base, at), in_global(P.stats, base, at);
+    in_global(P.x_coll, base, at), in_global(P.x_wall, base, at), in_global(P.wbase_wall, base, at);
+    if (P.dim == 2) group_run<2, false, kGroupBatchBlock>(P, A, lds, rank, size);
+    else group_run<3, false, kGroupBatchBlock>(P, A, lds, rank, size);
+    if (rank == 0 && threadIdx.x == 0) {
+        for (int k = 0; k < 3; ++k) P.stats[k] = (int)agent_load(&A.ctl->total[k]);
+        A.ctl->turn = (A.ctl->turn + (unsigned)K) % 3u;
+    }
+}
+
+// the words of n groups before a launch
+__global__ void k_group_arm(GroupCtl *c, int n) {
+    const int g = (int)blockIdx.x * (int)(blockDim.x / 4) + (int)(threadIdx.x >> 2), k = (int)(threadIdx.x & 3);
+    if (g >= n) return;
+    if (k == 0) c[g].reg = c[g].size = c[g].bar = 0u;
+    c[g].total[k] = 0u;
 }

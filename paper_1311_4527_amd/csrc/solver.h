@@ -183,6 +183,7 @@ struct twa_solver {
     float *group_xe = nullptr;
     unsigned char *group_sent = nullptr;
     int group_want = 0;
+    void *batch_ctl = nullptr; // shared words of this instance's group in its batch
     // TWA_F_TAPE: the state the differentiated run starts from (canonical
     // layouts), saved by create / set_init / set_state
     float *origin_z = nullptr, *origin_u = nullptr;

@@ -38,6 +38,7 @@
 #include <vector>
 
 #include "../../include/twa.h"
+#include "pairs.h"
 #include "prox.h"
 #include "solver.h"
 
@@ -2306,10 +2307,12 @@ twa_status iterate_tiny(twa_solver *s, int k) {
 
 constexpr unsigned kGroupLdsMax = 158u << 10; // of a compute unit's 160 KiB, less the kernel's own words
 
-// LDS layout of a group of `want` shares; false when it does not fit.
-bool group_layout(const twa_solver *s, int want, GroupLds *L, unsigned *bytes) {
+// LDS layout of a group of `want` shares, T lanes per workgroup; false when it
+// does not fit.
+bool group_layout(const twa_solver *s, int want, int T, GroupLds *L, unsigned *bytes) {
     const Params &P = s->P;
-    const long long items = P.cps * ((P.eta + kGroupCpw - 1) / kGroupCpw), units = (P.Fw + 31) / 32;
+    const long long items = (long long)group_items(P.p, (int)P.cps, T) * ((P.eta + kGroupCpw - 1) / kGroupCpw);
+    const long long units = (P.Fw + 31) / 32;
     L->items = (int)((items + want - 1) / want);
     L->walls32 = (int)((units + want - 1) / want);
     long long off = 0;
@@ -2322,10 +2325,11 @@ bool group_layout(const twa_solver *s, int want, GroupLds *L, unsigned *bytes) {
     L->zp = take(P.dense ? 16 * P.N : 0);
     L->rad = take(4LL * P.p);
     L->item = take(8LL * L->items);
-    L->word = take(8LL * L->items * kGroupCpw);
+    L->word = take(8LL * L->items * group_words(T));
     L->wbit = take(4LL * L->walls32);
-    L->q = take(P.Fc > 0 ? 4LL * kGroupQueue : 0);
-    L->qw = take(P.Fw > 0 ? 4LL * kGroupWallQueue : 0);
+    // (a share queues at most all its factors)
+    L->q = take(4LL * std::min<long long>(group_queue(T), (long long)L->items * group_words(T) * 64));
+    L->qw = take(4LL * std::min<long long>(group_wall_queue(T), 32LL * L->walls32));
     L->total = (unsigned)off;
     *bytes = (unsigned)off;
     return off <= (long long)kGroupLdsMax;
@@ -2359,7 +2363,7 @@ twa_status prepare_group(twa_solver *s) {
     while (want < 128 && P.Fc + P.Fw >= 2250LL * want) want *= 2;
     GroupLds L;
     unsigned bytes;
-    if (!group_layout(s, want, &L, &bytes)) return TWA_OK;
+    if (!group_layout(s, want, kGroupBlock, &L, &bytes)) return TWA_OK;
     GroupCtl *ctl;
     TRY(dev_alloc(s, &ctl, 1));
     TRY(dev_alloc(s, &s->group_acc, (size_t)3 * s->dim * P.N));
@@ -2379,10 +2383,14 @@ twa_status prepare_group(twa_solver *s) {
 constexpr int kGroupChunk = 1024; // iterations per launch at most
 
 // whether a wait inside a group ever ran out (copied behind the stream's work)
-twa_status group_stuck(twa_solver *s, unsigned *stuck) {
-    if (s->group_ctl)
-        HIP_TRY(s, hipMemcpyAsync(stuck, &static_cast<GroupCtl *>(s->group_ctl)->stuck, sizeof(unsigned),
-                                  hipMemcpyDeviceToHost, s->stream));
+twa_status group_stuck(twa_solver *s, unsigned (&stuck)[2]) {
+    const void *ctl[2] = {s->group_ctl, s->batch_ctl};
+    for (int k = 0; k < 2; ++k) {
+        stuck[k] = 0;
+        if (ctl[k])
+            HIP_TRY(s, hipMemcpyAsync(&stuck[k], &static_cast<const GroupCtl *>(ctl[k])->stuck, sizeof(unsigned),
+                                      hipMemcpyDeviceToHost, s->stream));
+    }
     return TWA_OK;
 }
 
@@ -2396,18 +2404,19 @@ twa_status iterate_group(twa_solver *s, int k) {
     A.cnt = s->group_cnt;
     A.xe = s->group_xe;
     A.sent = s->group_sent;
+    A.words = nullptr;
     A.want = s->group_want;
     // workgroups go to the 8 XCDs in turn: every 256 / want-th one keeps the
     // members on as few XCDs as their number allows (speed only)
     A.stride = 256 / A.want;
-    (void)group_layout(s, A.want, &A.L, &bytes);
+    (void)group_layout(s, A.want, kGroupBlock, &A.L, &bytes);
     Params P = s->P;
     P.rho = P.rho_prev = s->rho0;
     P.step = P.step_prev = s->alpha / s->rho0;
     const dim3 grid((unsigned)(A.want * A.stride)), block(kGroupBlock);
     while (k > 0) {
         A.K = std::min(k, kGroupChunk);
-        hipLaunchKernelGGL(k_group_arm, dim3(1), dim3(64), 0, s->stream, A.ctl);
+        hipLaunchKernelGGL(k_group_arm, dim3(1), dim3(64), 0, s->stream, A.ctl, 1);
         if (s->dim == 2) {
             if (P.dense) hipLaunchKernelGGL((k_group<2, true>), grid, block, bytes, s->stream, P, A);
             else hipLaunchKernelGGL((k_group<2, false>), grid, block, bytes, s->stream, P, A);
@@ -3218,11 +3227,11 @@ twa_status twa_get_stats(twa_solver *s, twa_stats *out) {
     HIP_TRY(s, hipMemcpyAsync(h, s->stats_dev, sizeof(int) * 3, hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(s, hipMemcpyAsync(&r, s->resid_dev, sizeof(unsigned), hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(s, hipMemcpyAsync(&overflow, s->P.counters + 5, sizeof(int), hipMemcpyDeviceToHost, s->stream));
-    unsigned stuck = 0;
-    TRY(group_stuck(s, &stuck));
+    unsigned stuck[2];
+    TRY(group_stuck(s, stuck));
     double obj = 0, clr = 0;
     TRY(twa_get_quality(s, &obj, &clr, nullptr)); // synchronises
-    if (stuck) return fail(s, TWA_E_DEVICE, "a group of workgroups gave up waiting for a member");
+    if (stuck[0] || stuck[1]) return fail(s, TWA_E_DEVICE, "a group of workgroups gave up waiting for a member");
     out->iter = s->iter;
     out->active_coll = h[0];
     out->active_wall = h[1];
@@ -3292,10 +3301,10 @@ twa_status twa_check_finite(twa_solver *s) {
     int bad = 0, overflow = 0;
     HIP_TRY(s, hipMemcpyAsync(&bad, s->bad_dev, sizeof(int), hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(s, hipMemcpyAsync(&overflow, s->P.counters + 5, sizeof(int), hipMemcpyDeviceToHost, s->stream));
-    unsigned stuck = 0;
-    TRY(group_stuck(s, &stuck));
+    unsigned stuck[2];
+    TRY(group_stuck(s, stuck));
     HIP_TRY(s, hipStreamSynchronize(s->stream));
-    if (stuck) return fail(s, TWA_E_DEVICE, "a group of workgroups gave up waiting for a member");
+    if (stuck[0] || stuck[1]) return fail(s, TWA_E_DEVICE, "a group of workgroups gave up waiting for a member");
     if (bad) return fail(s, TWA_E_NUMERIC, "non-finite value in z or u");
     if (overflow) return fail(s, TWA_E_NUMERIC, "consensus sum beyond its fixed-point range (diverging iterates)");
     return TWA_OK;
@@ -3317,6 +3326,14 @@ struct twa_batch {
     int2 *map_dev = nullptr;           // phased form: stream, queue, node block maps
     int n_stream = 0, n_queue = 0, n_nodes = 0;
     hipGraphExec_t pexec = nullptr;    // phased form: kPhasedChunk iterations
+    // block 0, steady iterations: a group of resident workgroups per instance
+    GroupArgs *groups_dev = nullptr;   // [n], and the blocks' instances behind it
+    const int *slots_dev = nullptr;
+    GroupCtl *ctl_dev = nullptr;
+    int n_slots = 0;                   // 0: not used
+    unsigned group_lds = 0;
+    void *group_mem = nullptr;
+    size_t group_bytes = 0;
     std::string err;
     twa_status latched = TWA_OK;
     hipGraphExec_t gexec = nullptr;
@@ -3385,6 +3402,122 @@ twa_status batch_bins(twa_batch *b) {
     return TWA_OK;
 }
 
+// The groups of a batch: shares by work, as many as the device holds at once
+// (workgroups past that would run after the first ones' last iteration; the
+// target grows until they fit, or every instance has one), and the blocks'
+// instances in an order that keeps a group on one XCD (blocks go to the 8 XCDs
+// in turn) and starts the large groups first.  A share has 1500 factors at
+// least, about six per lane: less and the barrier is most of the iteration.
+// Leaves n_slots 0, and the phased launches in use, where an instance does not
+// fit a workgroup's LDS, where there is no memory for the groups, and in the
+// dense form: it streams u of every factor, which the phased kernel has more
+// waves in flight for (64 instances 57 us per iteration, in groups 65; 16
+// instances 26 against 42).
+twa_status batch_groups(twa_batch *b) {
+    const int n = (int)b->solvers.size();
+    for (twa_solver *s : b->solvers)
+        if (s->P.dense) return TWA_OK;
+    const void *kernel = reinterpret_cast<const void *>(kp_group);
+    BHIP_TRY(b, hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGroupLdsMax));
+    int cus = 0;
+    BHIP_TRY(b, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->mem.device));
+    long long total = 0;
+    for (twa_solver *s : b->solvers) total += s->P.Fc + s->P.Fw;
+    std::vector<GroupArgs> g((size_t)n);
+    std::vector<std::pair<int, int>> order; // (-shares, instance)
+    for (double target = std::max(1500.0, (double)total / (3.0 * cus));; target *= 1.1) {
+        order.clear();
+        b->group_lds = 0;
+        long long slots = 0, most = 0;
+        for (int i = 0; i < n; ++i) {
+            twa_solver *s = b->solvers[i];
+            unsigned bytes;
+            g[i].want = (int)std::min<long long>(64, std::max<long long>(1, (long long)std::ceil((s->P.Fc + s->P.Fw) / target)));
+            g[i].stride = 1;
+            g[i].K = 0;
+            if (!group_layout(s, g[i].want, kGroupBatchBlock, &g[i].L, &bytes)) return TWA_OK;
+            b->group_lds = std::max(b->group_lds, bytes);
+            order.emplace_back(-g[i].want, i);
+            slots += g[i].want;
+            most = std::max<long long>(most, g[i].want);
+        }
+        int per_cu = 0;
+        BHIP_TRY(b, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kGroupBatchBlock, b->group_lds));
+        if (slots <= (long long)std::max(1, per_cu) * cus || most == 1) break;
+    }
+    std::stable_sort(order.begin(), order.end());
+    std::vector<std::vector<int>> column(8);
+    for (const auto &o : order) {
+        auto &c = *std::min_element(column.begin(), column.end(),
+                                    [](const std::vector<int> &x, const std::vector<int> &y) { return x.size() < y.size(); });
+        c.insert(c.end(), (size_t)-o.first, o.second);
+    }
+    std::vector<int> slots;
+    for (size_t r = 0;; ++r) {
+        bool any = false;
+        for (const auto &c : column) any = any || r < c.size();
+        if (!any) break;
+        for (const auto &c : column) slots.push_back(r < c.size() ? c[r] : -1);
+    }
+    // one buffer: the arguments, the slots, the words, sums, counts, x and sent
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = off;
+        off += (bytes + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t o_args = take(sizeof(GroupArgs) * n), o_slots = take(sizeof(int) * slots.size());
+    const size_t zero0 = take(sizeof(GroupCtl) * n), o_ctl = zero0;
+    std::vector<size_t> o_acc(n), o_cnt(n), o_xe(n), o_sent(n), o_words(n);
+    for (int i = 0; i < n; ++i) {
+        const Params &P = b->solvers[i]->P;
+        o_acc[i] = take(sizeof(unsigned long long) * 3 * P.dim * P.N);
+        o_cnt[i] = take(sizeof(int) * 3 * P.N);
+    }
+    const size_t zero1 = off;
+    for (int i = 0; i < n; ++i) {
+        const Params &P = b->solvers[i]->P;
+        o_xe[i] = take(sizeof(float) * (P.Fe * 2 + (P.vo ? P.p : 0)) * P.dim);
+        o_sent[i] = take((size_t)P.Fe);
+        o_words[i] = take(sizeof(unsigned long long) * g[i].want * g[i].L.items * group_words(kGroupBatchBlock));
+    }
+    b->group_mem = b->mem.get(off, b->stream);
+    if (!b->group_mem) return TWA_OK;
+    b->group_bytes = off;
+    char *m = static_cast<char *>(b->group_mem);
+    for (int i = 0; i < n; ++i) {
+        g[i].ctl = reinterpret_cast<GroupCtl *>(m + o_ctl) + i;
+        g[i].acc = reinterpret_cast<unsigned long long *>(m + o_acc[i]);
+        g[i].cnt = reinterpret_cast<int *>(m + o_cnt[i]);
+        g[i].xe = reinterpret_cast<float *>(m + o_xe[i]);
+        g[i].sent = reinterpret_cast<unsigned char *>(m + o_sent[i]);
+        g[i].words = reinterpret_cast<unsigned long long *>(m + o_words[i]);
+    }
+    BHIP_TRY(b, hipMemsetAsync(m + zero0, 0, zero1 - zero0, b->stream));
+    BHIP_TRY(b, hipMemcpyAsync(m + o_args, g.data(), sizeof(GroupArgs) * n, hipMemcpyHostToDevice, b->stream));
+    BHIP_TRY(b, hipMemcpyAsync(m + o_slots, slots.data(), sizeof(int) * slots.size(), hipMemcpyHostToDevice, b->stream));
+    BHIP_TRY(b, hipStreamSynchronize(b->stream)); // the sources are on this stack
+    b->groups_dev = reinterpret_cast<GroupArgs *>(m + o_args);
+    b->slots_dev = reinterpret_cast<const int *>(m + o_slots);
+    b->ctl_dev = reinterpret_cast<GroupCtl *>(m + o_ctl);
+    b->n_slots = (int)slots.size();
+    for (int i = 0; i < n; ++i) b->solvers[i]->batch_ctl = b->ctl_dev + i;
+    return TWA_OK;
+}
+
+// k steady iterations of every instance in its group
+void launch_groups(twa_batch *b, int k) {
+    const int n = (int)b->solvers.size();
+    while (k > 0) {
+        const int K = std::min(k, kGroupChunk);
+        hipLaunchKernelGGL(k_group_arm, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, b->stream, b->ctl_dev, n);
+        hipLaunchKernelGGL(kp_group, dim3(b->n_slots), dim3(kGroupBatchBlock), b->group_lds, b->stream,
+                           (const Params *)b->insts_dev, (const GroupArgs *)b->groups_dev, b->slots_dev, K,
+                           reinterpret_cast<char *>(b->insts_dev), reinterpret_cast<unsigned long long>(b->insts_dev));
+        k -= K;
+    }
+}
+
 constexpr int kPhasedChunk = 32;
 
 void launch_batch(twa_batch *b, int k, int first) {
@@ -3435,6 +3568,7 @@ void twa_batch_destroy(twa_batch *b) {
     b->mem.put(b->bin_start_dev, sizeof(int) * (n + 1), b->stream);
     b->mem.put(b->bin_items_dev, sizeof(int) * n, b->stream);
     b->mem.put(b->map_dev, b->map_bytes, b->stream);
+    b->mem.put(b->group_mem, b->group_bytes, b->stream);
     if (b->pexec) (void)hipGraphExecDestroy(b->pexec);
     if (b->own_stream) (void)hipStreamDestroy(b->own_stream);
     delete b;
@@ -3528,6 +3662,11 @@ twa_status twa_batch_create(int n, const twa_instance *inst, unsigned flags, voi
         twa_batch_destroy(b);
         return TWA_E_DEVICE;
     }
+    const twa_status gst = batch_groups(b);
+    if (gst != TWA_OK) {
+        twa_batch_destroy(b);
+        return gst;
+    }
     *out = b;
     return TWA_OK;
 }
@@ -3600,6 +3739,10 @@ twa_status twa_batch_iterate(twa_batch *b, int k) {
         if (first) {
             launch_batch(b, 1, 1);
             --left;
+        }
+        if (left > 0 && b->n_slots > 0) {
+            launch_groups(b, left);
+            left = 0;
         }
         if (left >= kPhasedChunk && !b->pexec) {
             hipGraph_t g = nullptr;
