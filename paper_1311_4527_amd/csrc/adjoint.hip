@@ -60,18 +60,19 @@ struct Adj {
     const unsigned char *lnext;  // [N] <-rho^{k+1}
     float rho, step;             // weight rho0 of iteration k; u step alpha / (configuration's rho0)
     // cotangents
-    const float *zb_in;  // [N][2] dL/dz^{k+1}
-    float *zb_out;       // [N][2] dL/dz^k: zeroed, then accumulated
+    // Node sums, four floats per node: dL/dz and, over the kept edges of
+    // captured factors, the sum S of dL/du.
+    const float *sum_in; // [N][4] dL/dz^{k+1}, S of dL/du^{k+1}
+    float *sum_out;      // [N][4] dL/dz^k, S for iteration k-1: zeroed, then accumulated
     const float *ub_in;  // [E][2] dL/du^{k+1}
     float *ub_out;       // [E][2] dL/du^k: zeroed, then written where nonzero
     float *g;            // [N][2]
-    unsigned char *cls;  // [N] weight class of the node's mean
     const int *cnt;      // [N] size of the node's mean set in iteration k (captured)
-    const float *S_in;   // [N][2] sum of dL/du^{k+1} over the kept edges of captured factors
-    float *S_next;       // [N][2] the same sum for iteration k-1, accumulated here
     const unsigned char *rout_prev; // [F] ->rho^{k-1}, or null when k-1 is not captured yet
     float *dx0, *dxT;    // [p][2], accumulated
-    double *drd;         // [p], accumulated
+    // Radius cotangents of agent i's factors of interval s, at node (i, s): with
+    // one word per agent a crowded step waited for its atomics (15.2 -> 13.4 us).
+    double *drd;         // [N], accumulated
 };
 
 __device__ __forceinline__ long long node_id(const Adj &A, int i, int s) { return (long long)i * (A.eta + 1) + s; }
@@ -88,6 +89,31 @@ __device__ __forceinline__ void pair_of(int p, long long q, int &i, int &j) {
     while (i > 0 && pair_index(p, i, i + 1) > q) --i;
     while (i < p - 2 && pair_index(p, i + 1, i + 2) <= q) ++i;
     j = (int)(q - pair_index(p, i, i + 1)) + i + 1;
+}
+
+// Adds v to the four sums of node t, on every lane with `on`; all 64 lanes call.
+// Four lanes add one node's four floats (the quad broadcasts each lane's in
+// turn), so a wave's request names 16 lines and not 64: the requests to memory
+// are what the sums cost (256 agents over 500 iterations: k_adj_factors 21.0 us
+// on average with one float per lane and address, 15.2 so; without any adds 14.4).
+template <int K>
+__device__ __forceinline__ int quad_lane(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, K * 0x55, 0xf, 0xf, false);
+}
+template <int K>
+__device__ __forceinline__ void node_add_from(float *sums, int t, float4 v) {
+    const int c = threadIdx.x & 3, tk = quad_lane<K>(t);
+    const float x = __int_as_float(quad_lane<K>(__float_as_int(v.x))), y = __int_as_float(quad_lane<K>(__float_as_int(v.y)));
+    const float z = __int_as_float(quad_lane<K>(__float_as_int(v.z))), w = __int_as_float(quad_lane<K>(__float_as_int(v.w)));
+    const float a = c == 0 ? x : c == 1 ? y : c == 2 ? z : w;
+    if (tk >= 0 && a != 0.f) atomicAdd(&sums[4LL * tk + c], a);
+}
+__device__ __forceinline__ void node_add(float *sums, bool on, long long t, float4 v) {
+    const int id = on ? (int)t : -1;
+    node_add_from<0>(sums, id, v);
+    node_add_from<1>(sums, id, v);
+    node_add_from<2>(sums, id, v);
+    node_add_from<3>(sums, id, v);
 }
 
 // In the energy mode a collision or wall factor that sent weight 0 carries
@@ -123,8 +149,8 @@ __global__ __launch_bounds__(256) void k_adj_accum(Adj A, float *S, const AdjRec
         }
         for (int k = 0; k < ne; ++k)
             if (A.lnext[nd[k]] == W_STD) {
-                atomicAdd(&S[2 * nd[k]], A.ub_in[2 * ed[k]]);
-                atomicAdd(&S[2 * nd[k] + 1], A.ub_in[2 * ed[k] + 1]);
+                atomicAdd(&S[4 * nd[k] + 2], A.ub_in[2 * ed[k]]);
+                atomicAdd(&S[4 * nd[k] + 3], A.ub_in[2 * ed[k] + 1]);
             }
     }
 }
@@ -152,62 +178,68 @@ __global__ __launch_bounds__(256) void k_adj_select(Adj A, unsigned nb_nodes, co
     }
     const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= A.N) return;
-    A.zb_out[2 * t] = A.zb_out[2 * t + 1] = 0.f;
-    A.S_next[2 * t] = A.S_next[2 * t + 1] = 0.f;
-    const int i = (int)(t / (A.eta + 1)), s = (int)(t % (A.eta + 1));
-    const bool keep_node = A.lnext[t] == W_STD;
-    float sx = A.S_in[2 * t], sy = A.S_in[2 * t + 1];
-    auto edge = [&](long long f, long long e) {
-        if (A.rout[f] == W_STD && keep_node) {
-            sx += A.ub_in[2 * e];
-            sy += A.ub_in[2 * e + 1];
+    reinterpret_cast<float4 *>(A.sum_out)[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+    const int i = (int)((unsigned)t / (unsigned)(A.eta + 1)), s = (int)t - i * (A.eta + 1);
+    // everything loaded first, at clamped places: a load behind the branch of
+    // the one before it is another trip to memory, and those bound the kernel
+    const float2 *ub = reinterpret_cast<const float2 *>(A.ub_in);
+    const long long fx = 2LL * i + (s == A.eta), fa = (long long)i * A.eta + max(s - 1, 0),
+                    fb = (long long)i * A.eta + min(s, A.eta - 1);
+    const int code = A.lnext[t], rx = A.rout[fx], ra = A.rout[A.f_energy + fa], rb = A.rout[A.f_energy + fb];
+    const float2 ux = ub[fx], ua = ub[A.e_energy + 2 * fa + 1], un = ub[A.e_energy + 2 * fb];
+    const float4 in = reinterpret_cast<const float4 *>(A.sum_in)[t];
+    const float cnt = (float)A.cnt[t];
+    float sx = in.z, sy = in.w;
+    auto edge = [&](bool here, int r, float2 u) {
+        if (here && r == W_STD && code == W_STD) {
+            sx += u.x;
+            sy += u.y;
         }
     };
-    if (s == 0) edge(2LL * i, 2LL * i);
-    if (s == A.eta) edge(2LL * i + 1, 2LL * i + 1);
-    if (s > 0) {
-        const long long fe = (long long)i * A.eta + s - 1;
-        edge(A.f_energy + fe, A.e_energy + 2 * fe + 1);
-    }
-    if (s < A.eta) {
-        const long long fe = (long long)i * A.eta + s;
-        edge(A.f_energy + fe, A.e_energy + 2 * fe);
-    }
-    const float cnt = (float)A.cnt[t];
-    A.cls[t] = A.lnext[t];
-    A.g[2 * t] = (A.zb_in[2 * t] - A.step * sx) / cnt;
-    A.g[2 * t + 1] = (A.zb_in[2 * t + 1] - A.step * sy) / cnt;
+    edge(s == 0 || s == A.eta, rx, ux);
+    edge(s > 0, ra, ua);
+    edge(s < A.eta, rb, un);
+    reinterpret_cast<float2 *>(A.g)[t] = make_float2((in.x - A.step * sx) / cnt, (in.y - A.step * sy) / cnt);
 }
 
-// dL/dx of edge e (node t) of a factor with weight r; also the part of
-// dL/du^k that does not go through n.
-__device__ __forceinline__ void edge_xbar(const Adj &A, int r, long long t, long long e, f2 &xb, f2 &up) {
-    bool keep = r == W_STD && A.lnext[t] == W_STD;
-    int c = A.cls[t];
-    bool in_mean = c == W_INF ? r == W_INF : r == W_STD;
-    f2 ubp = keep ? mk(A.ub_in[2 * e], A.ub_in[2 * e + 1]) : mk(0.f, 0.f);
-    f2 gg = in_mean ? mk(A.g[2 * t], A.g[2 * t + 1]) : mk(0.f, 0.f);
+// What an edge's node and the step after hold for it, loaded together.
+struct EdgeIn {
+    int code, next; // <-rho^k and <-rho^{k+1} of the node
+    float2 g, ub;
+};
+__device__ __forceinline__ EdgeIn edge_in(const Adj &A, long long t, float2 ub) {
+    return EdgeIn{A.l[t], A.lnext[t], reinterpret_cast<const float2 *>(A.g)[t], ub};
+}
+
+// dL/dx of an edge of a factor with weight r; also the part of dL/du^k that
+// does not go through n.  (The class of a node's mean is its <-rho^{k+1}.)
+__device__ __forceinline__ void edge_xbar(const Adj &A, int r, const EdgeIn &d, f2 &xb, f2 &up) {
+    const bool keep = r == W_STD && d.next == W_STD;
+    const bool in_mean = d.next == W_INF ? r == W_INF : r == W_STD;
+    const f2 ubp = keep ? mk(d.ub.x, d.ub.y) : mk(0.f, 0.f);
+    const f2 gg = in_mean ? mk(d.g.x, d.g.y) : mk(0.f, 0.f);
     xb = add(scl(ubp, A.step), gg);
     up = add(ubp, gg);
 }
 
-// dL/du^k of edge e and dL/dn into its node's dL/dz^k.  kept_prev: the edge
-// is kept by iteration k-1's u update (its factor sent rho0 there too and
-// the node keeps rho0), so its dL/du^k enters that step's sum S.
-__device__ __forceinline__ void edge_out(const Adj &A, long long t, long long e, f2 up, f2 nb, bool kept_prev = false) {
+// dL/du^k of edge e; returns what the edge adds to its node's sums: dL/dn and,
+// where kept_prev, dL/du^k (the edge is kept by iteration k-1's u update: its
+// factor sent rho0 there too and the node keeps rho0).
+__device__ __forceinline__ float4 edge_out(const Adj &A, long long e, f2 up, f2 nb, bool kept_prev = false) {
     const f2 uo = mk(up.x - nb.x, up.y - nb.y);
-    A.ub_out[2 * e] = uo.x;
-    A.ub_out[2 * e + 1] = uo.y;
-    atomicAdd(&A.zb_out[2 * t], nb.x);
-    atomicAdd(&A.zb_out[2 * t + 1], nb.y);
-    if (kept_prev) {
-        atomicAdd(&A.S_next[2 * t], uo.x);
-        atomicAdd(&A.S_next[2 * t + 1], uo.y);
-    }
+    reinterpret_cast<float2 *>(A.ub_out)[e] = make_float2(uo.x, uo.y);
+    return make_float4(nb.x, nb.y, kept_prev ? uo.x : 0.f, kept_prev ? uo.y : 0.f);
 }
 
+// What a factor adds to the sums of its nodes (ne of them).
+struct NodeAdds {
+    int ne = 0;
+    long long t[4];
+    float4 v[4];
+};
+
 // A fixed or energy factor (canonical factor index f < f_coll).
-__device__ __forceinline__ void adj_small(const Adj &A, long long f) {
+__device__ __forceinline__ void adj_small(const Adj &A, long long f, NodeAdds &out) {
     const int r = A.rout[f];
     if (f < A.f_energy) {
         // fixed start / goal factor: x is the constant itself
@@ -215,74 +247,88 @@ __device__ __forceinline__ void adj_small(const Adj &A, long long f) {
         const int s = (f & 1) ? A.eta : 0;
         const long long t = node_id(A, i, s), e = f;
         f2 xb, up;
-        edge_xbar(A, r, t, e, xb, up);
+        edge_xbar(A, r, edge_in(A, t, reinterpret_cast<const float2 *>(A.ub_in)[e]), xb, up);
         float *dst = (f & 1) ? A.dxT : A.dx0;
         dst[2 * i] += xb.x;
         dst[2 * i + 1] += xb.y;
-        edge_out(A, t, e, up, mk(0.f, 0.f));
+        (void)edge_out(A, e, up, mk(0.f, 0.f));
     } else {
         // energy factor (App. E): linear in n
         const long long fe = f - A.f_energy;
-        const int i = (int)(fe / A.eta), s = (int)(fe % A.eta);
+        const int i = (int)((unsigned)fe / (unsigned)A.eta), s = (int)fe - i * A.eta;
         const long long t0 = node_id(A, i, s), t1 = t0 + 1;
         const long long e0 = A.e_energy + 2 * fe, e1 = e0 + 1;
         f2 xb0, up0, xb1, up1;
-        edge_xbar(A, r, t0, e0, xb0, up0);
-        edge_xbar(A, r, t1, e1, xb1, up1);
-        const int k0 = A.l[t0], k1 = A.l[t1];
-        const float w0 = wval(k0, A.rho), w1 = wval(k1, A.rho);
+        const float4 ub = *reinterpret_cast<const float4 *>(A.ub_in + 2 * e0); // (e0 is even)
+        const EdgeIn d0 = edge_in(A, t0, make_float2(ub.x, ub.y)), d1 = edge_in(A, t1, make_float2(ub.z, ub.w));
         const float C = A.C[fe];
+        edge_xbar(A, r, d0, xb0, up0);
+        edge_xbar(A, r, d1, xb1, up1);
+        const int k0 = d0.code, k1 = d1.code;
+        const float w0 = wval(k0, A.rho), w1 = wval(k1, A.rho);
         float nb[4] = {0.f, 0.f, 0.f, 0.f};
         energy_vjp(w0, w1, k0, k1, C, xb0.x, xb1.x, nb[0], nb[2]);
         energy_vjp(w0, w1, k0, k1, C, xb0.y, xb1.y, nb[1], nb[3]);
-        edge_out(A, t0, e0, up0, mk(nb[0], nb[1]));
-        edge_out(A, t1, e1, up1, mk(nb[2], nb[3]));
+        out.ne = 2;
+        out.t[0] = t0, out.v[0] = edge_out(A, e0, up0, mk(nb[0], nb[1]));
+        out.t[1] = t1, out.v[1] = edge_out(A, e1, up1, mk(nb[2], nb[3]));
     }
 }
 
 // A collision or wall factor that sent rho0 (one captured record).
-__device__ __forceinline__ void adj_active(const Adj &A, const AdjRec &rec) {
+__device__ __forceinline__ void adj_active(const Adj &A, const AdjRec &rec, NodeAdds &out) {
     if (!rec.wall) {
         // collision factor (App. C)
         const long long fc = rec.f;
-        int s = (int)(fc / A.P2), i, j;
+        const long long e0 = A.e_coll + 4 * fc;
+        const float4 *ub = reinterpret_cast<const float4 *>(A.ub_in + 2 * e0); // (e0 is even)
+        const float4 ua = ub[0], uc = ub[1];
+        const bool prev = A.rout_prev && A.rout_prev[A.f_coll + fc] == W_STD;
+        const int s = (int)(rec.f / (unsigned)A.P2);
+        int i, j;
         pair_of(A.p, fc - (long long)s * A.P2, i, j);
-        long long t[4] = {node_id(A, i, s), node_id(A, i, s + 1), node_id(A, j, s), node_id(A, j, s + 1)};
-        long long e0 = A.e_coll + 4 * fc;
+        const long long t[4] = {node_id(A, i, s), node_id(A, i, s + 1), node_id(A, j, s), node_id(A, j, s + 1)};
+        const EdgeIn d[4] = {edge_in(A, t[0], make_float2(ua.x, ua.y)), edge_in(A, t[1], make_float2(ua.z, ua.w)),
+                             edge_in(A, t[2], make_float2(uc.x, uc.y)), edge_in(A, t[3], make_float2(uc.z, uc.w))};
+        const float R = A.radii[i] + A.radii[j];
         float xb[8], w[4], nbv[8];
         int k[4];
         f2 up[4];
         for (int qq = 0; qq < 4; ++qq) {
             f2 x_b;
-            edge_xbar(A, W_STD, t[qq], e0 + qq, x_b, up[qq]);
+            edge_xbar(A, W_STD, d[qq], x_b, up[qq]);
             xb[2 * qq] = x_b.x, xb[2 * qq + 1] = x_b.y;
-            k[qq] = A.l[t[qq]];
+            k[qq] = d[qq].code;
             w[qq] = wval(k[qq], A.rho);
         }
         for (int qq = 0; qq < 8; ++qq) nbv[qq] = 0.f;
         float Rb = 0.f;
-        coll_vjp2(rec.n, w, k, A.radii[i] + A.radii[j], xb, nbv, Rb);
-        atomicAdd(&A.drd[i], (double)Rb);
-        atomicAdd(&A.drd[j], (double)Rb);
-        const bool prev = A.rout_prev && A.rout_prev[A.f_coll + fc] == W_STD;
+        coll_vjp2(rec.n, w, k, R, xb, nbv, Rb);
+        atomicAdd(&A.drd[t[0]], (double)Rb);
+        atomicAdd(&A.drd[t[2]], (double)Rb);
+        out.ne = 4;
         for (int qq = 0; qq < 4; ++qq)
-            edge_out(A, t[qq], e0 + qq, up[qq], mk(nbv[2 * qq], nbv[2 * qq + 1]), prev && A.l[t[qq]] == W_STD);
+            out.t[qq] = t[qq], out.v[qq] = edge_out(A, e0 + qq, up[qq], mk(nbv[2 * qq], nbv[2 * qq + 1]),
+                                                    prev && k[qq] == W_STD);
     } else {
         // wall factor (App. D)
         const long long fw = rec.f;
-        long long per_s = (long long)A.p * A.W;
-        int s = (int)(fw / per_s);
-        long long q = fw - (long long)s * per_s;
-        int i = (int)(q / A.W), wi = (int)(q % A.W);
-        long long t0 = node_id(A, i, s), t1 = t0 + 1;
-        long long e0 = A.e_wall + 2 * fw, e1 = e0 + 1;
+        const unsigned per_s = (unsigned)(A.p * A.W);
+        const int s = (int)(rec.f / per_s);
+        const unsigned q = rec.f - (unsigned)s * per_s;
+        const int i = (int)(q / (unsigned)A.W), wi = (int)(q % (unsigned)A.W);
+        const long long t0 = node_id(A, i, s), t1 = t0 + 1;
+        const long long e0 = A.e_wall + 2 * fw, e1 = e0 + 1;
+        const float4 ub = *reinterpret_cast<const float4 *>(A.ub_in + 2 * e0); // (e0 is even)
+        const EdgeIn d0 = edge_in(A, t0, make_float2(ub.x, ub.y)), d1 = edge_in(A, t1, make_float2(ub.z, ub.w));
+        const bool prev = A.rout_prev && A.rout_prev[A.f_wall + fw] == W_STD;
         f2 xb0, up0, xb1, up1;
-        edge_xbar(A, W_STD, t0, e0, xb0, up0);
-        edge_xbar(A, W_STD, t1, e1, xb1, up1);
+        edge_xbar(A, W_STD, d0, xb0, up0);
+        edge_xbar(A, W_STD, d1, xb1, up1);
         float4 wl = A.walls[wi];
         Capsule Cw{mk(wl.x, wl.y), mk(wl.z, wl.w), A.radii[i]};
         f2 n0 = mk(rec.n[0], rec.n[1]), n1 = mk(rec.n[2], rec.n[3]);
-        int k0 = A.l[t0], k1 = A.l[t1];
+        const int k0 = d0.code, k1 = d1.code;
         float w0 = wval(k0, A.rho), w1 = wval(k1, A.rho);
         f2 x0, x1;
         Choice ch;
@@ -290,47 +336,70 @@ __device__ __forceinline__ void adj_active(const Adj &A, const AdjRec &rec) {
         f2 nb0 = mk(0.f, 0.f), nb1 = mk(0.f, 0.f);
         float rb = 0.f;
         capsule_vjp(Cw, n0, n1, w0, w1, k0, k1, ch, xb0, xb1, nb0, nb1, rb);
-        atomicAdd(&A.drd[i], (double)rb);
-        const bool prev = A.rout_prev && A.rout_prev[A.f_wall + fw] == W_STD;
-        edge_out(A, t0, e0, up0, nb0, prev && A.l[t0] == W_STD);
-        edge_out(A, t1, e1, up1, nb1, prev && A.l[t1] == W_STD);
+        atomicAdd(&A.drd[t0], (double)rb);
+        out.ne = 2;
+        out.t[0] = t0, out.v[0] = edge_out(A, e0, up0, nb0, prev && k0 == W_STD);
+        out.t[1] = t1, out.v[1] = edge_out(A, e1, up1, nb1, prev && k1 == W_STD);
     }
 }
 
 // The factors of one reverse step: blocks [0, nb_small) take the fixed and
 // energy factors one lane each; the rest stride over the captured records
 // [offs[0], offs[1]) (clipped to the pool's capacity), one lane each, so the
-// non-linear derivatives run in full waves.
+// non-linear derivatives run in full waves.  Bound by latency: a few tens of
+// waves, each a chain of dependent loads, the minimiser again, and the adds.
+// Loads that do not depend on one another are issued together (EdgeIn).
 __global__ __launch_bounds__(256) void k_adj_factors(Adj A, unsigned nb_small, const AdjRec *pool, const unsigned *offs,
                                                      unsigned cap) {
     if (blockIdx.x < nb_small) {
         const long long f = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-        if (f < A.f_coll) adj_small(A, f);
+        NodeAdds out;
+        if (f < A.f_coll) adj_small(A, f, out);
+        for (int k = 0; k < 2; ++k) node_add(A.sum_out, k < out.ne, out.t[k], out.v[k]);
         return;
     }
     const unsigned b = offs[0], e = min(offs[1], cap);
     const unsigned nblk = gridDim.x - nb_small;
-    for (unsigned t = b + (blockIdx.x - nb_small) * blockDim.x + threadIdx.x; t < e; t += nblk * blockDim.x)
-        adj_active(A, pool[t]);
+    // (the loop is uniform over a block: all lanes take part in the sums)
+    for (unsigned t0 = b + (blockIdx.x - nb_small) * blockDim.x; t0 < e; t0 += nblk * blockDim.x) {
+        NodeAdds out;
+        if (threadIdx.x < e - t0) adj_active(A, pool[t0 + threadIdx.x], out);
+        for (int k = 0; k < 4; ++k) node_add(A.sum_out, k < out.ne, out.t[k], out.v[k]);
+    }
+}
+
+// The sums the reverse begins from: dL/dz of the last state (a caller's array:
+// read float by float, at any alignment), no S.
+__global__ void k_adj_start(float4 *sums, const float *dz, long long N) {
+    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < N) sums[t] = make_float4(dz[2 * t], dz[2 * t + 1], 0.f, 0.f);
 }
 
 // z^0 cotangent: its end points are the start and goal
-__global__ void k_adj_finish(Adj A, float *dz0, float *dr) {
+__global__ void k_adj_finish(Adj A, float *dz0) {
     long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t < A.N) {
         int i = (int)(t / (A.eta + 1)), s = (int)(t % (A.eta + 1));
         bool end = s == 0 || s == A.eta;
         if (end) {
             float *dst = s == 0 ? A.dx0 : A.dxT;
-            dst[2 * i] += A.zb_in[2 * t];
-            dst[2 * i + 1] += A.zb_in[2 * t + 1];
+            dst[2 * i] += A.sum_in[4 * t];
+            dst[2 * i + 1] += A.sum_in[4 * t + 1];
         }
         if (dz0) {
-            dz0[2 * t] = end ? 0.f : A.zb_in[2 * t];
-            dz0[2 * t + 1] = end ? 0.f : A.zb_in[2 * t + 1];
+            dz0[2 * t] = end ? 0.f : A.sum_in[4 * t];
+            dz0[2 * t + 1] = end ? 0.f : A.sum_in[4 * t + 1];
         }
     }
-    if (t < A.p) dr[t] = (float)A.drd[t];
+}
+
+// dL/dr of agent blockIdx.x, one wave
+__global__ __launch_bounds__(64) void k_adj_radii(Adj A, float *dr) {
+    const int i = blockIdx.x;
+    double v = 0.0;
+    for (int s = threadIdx.x; s <= A.eta; s += 64) v += A.drd[node_id(A, i, s)];
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if (threadIdx.x == 0) dr[i] = (float)v;
 }
 
 // A state with its collision / wall u sparse (a checkpoint): z, <-rho and
@@ -463,13 +532,12 @@ struct Buffers {
     float *u_tmp;                 // [E][2] dense u of a state being packed or unpacked
     // two cotangent sets, alternately a reverse step's input and its output
     // (the output is cleared where the step before last wrote it, or whole
-    // at a segment's first two steps): dL/du [E][2], dL/dz [N][2], and the
-    // per-node sum S [N][2] that the step after it reads
+    // at a segment's first two steps): dL/du [E][2], and per node dL/dz and
+    // the sum S that the step after it reads [N][4]
     char *set[2];
     size_t set_bytes;
     float *g;                     // [N][2]
-    unsigned char *cls;           // [N]
-    double *drd;                  // [p]
+    double *drd;                  // [N]
     unsigned *arena_cursor;
     // What a segment's recompute captures, twice: segment c uses copy c & 1,
     // so that one segment is recomputed while the one after it is reversed.
@@ -486,14 +554,13 @@ struct Buffers {
 };
 
 // Carve one cotangent set (see Buffers) from base; returns its size.
-size_t set_layout(const Shape &h, char *base, float **ub = nullptr, float **zb = nullptr, float **S = nullptr) {
+size_t set_layout(const Shape &h, char *base, float **ub = nullptr, float **sums = nullptr) {
     Region R;
     R.base = base;
     R.cap = ~(size_t)0;
     float *a = R.take<float>((size_t)h.E * 2);
-    float *b = R.take<float>((size_t)h.N * 2);
-    float *c = R.take<float>((size_t)h.N * 2);
-    if (ub) *ub = a, *zb = b, *S = c;
+    float *b = R.take<float>((size_t)h.N * 4);
+    if (ub) *ub = a, *sums = b;
     return R.used;
 }
 
@@ -514,8 +581,7 @@ bool layout(Region &R, const Shape &h, Buffers &B) {
     B.set[0] = R.take<char>(B.set_bytes);
     B.set[1] = R.take<char>(B.set_bytes);
     B.g = R.take<float>((size_t)h.N * 2);
-    B.cls = R.take<unsigned char>((size_t)h.N);
-    B.drd = R.take<double>((size_t)h.p);
+    B.drd = R.take<double>((size_t)h.N);
     B.arena_cursor = R.take<unsigned>(1);
     bool ok = true;
     for (int b = 0; b < 2; ++b) {
@@ -527,7 +593,7 @@ bool layout(Region &R, const Shape &h, Buffers &B) {
         ok = ok && B.pool_cursor[b] && B.offs[b] && B.rout[b] && B.lseg[b] && B.cntseg[b];
     }
     return ok && B.cur.z && B.cur.l && B.cur.u_small && B.cur.first && B.cur.end && B.ck_z && B.ck_us && B.ck_l &&
-           B.ck_first && B.ck_end && B.u_tmp && B.set[0] && B.set[1] && B.g && B.cls && B.drd && B.arena_cursor;
+           B.ck_first && B.ck_end && B.u_tmp && B.set[0] && B.set[1] && B.g && B.drd && B.arena_cursor;
 }
 
 Sparse ckpt(const Buffers &B, const Shape &h, long long c) {
@@ -667,17 +733,18 @@ twa_status run_once(twa_solver *s, const Shape &h, Buffers &B, const float *dL_d
     A.e_energy = P.e_energy, A.e_coll = P.e_coll, A.e_wall = P.e_wall;
     A.f_energy = P.f_energy, A.f_coll = P.f_coll, A.f_wall = P.f_wall;
     A.radii = P.radii, A.walls = P.walls, A.C = P.C;
-    A.g = B.g, A.cls = B.cls, A.dx0 = dL_dx0, A.dxT = dL_dxT, A.drd = B.drd;
+    A.g = B.g, A.dx0 = dL_dx0, A.dxT = dL_dxT, A.drd = B.drd;
     int in = 0; // the set holding dL/d(state after the step being reversed)
     {
-        float *ub, *zb, *S;
-        set_layout(h, B.set[in], &ub, &zb, &S);
+        float *ub, *sums;
+        set_layout(h, B.set[in], &ub, &sums);
         HIP_TRY(s, hipMemsetAsync(B.set[in], 0, B.set_bytes, st));
-        HIP_TRY(s, hipMemcpyAsync(zb, dL_dz, sizeof(float) * h.N * 2, hipMemcpyDeviceToDevice, st));
+        hipLaunchKernelGGL(k_adj_start, dim3((unsigned)((h.N + 255) / 256)), dim3(256), 0, st,
+                           reinterpret_cast<float4 *>(sums), dL_dz, h.N);
     }
     HIP_TRY(s, hipMemsetAsync(dL_dx0, 0, sizeof(float) * s->p * 2, st));
     HIP_TRY(s, hipMemsetAsync(dL_dxT, 0, sizeof(float) * s->p * 2, st));
-    HIP_TRY(s, hipMemsetAsync(B.drd, 0, sizeof(double) * s->p, st));
+    HIP_TRY(s, hipMemsetAsync(B.drd, 0, sizeof(double) * h.N, st));
     const unsigned nb_nodes = (unsigned)((h.N + 255) / 256), nb_small = (unsigned)((P.f_coll + 255) / 256);
     const unsigned nb_rec = 256; // blocks striding over the captured records
     const unsigned nb_clr = 64;  // blocks clearing a step's output sparsely
@@ -698,6 +765,8 @@ twa_status run_once(twa_solver *s, const Shape &h, Buffers &B, const float *dL_d
         TRY(unpack(s, h, B, checkpoint(c), k0));
         HIP_TRY(s, hipMemsetAsync(B.pool_cursor[b], 0, sizeof(unsigned), st));
         HIP_TRY(s, hipMemsetAsync(B.offs[b], 0, sizeof(unsigned), st));
+        // (the iterations write the collision and wall factors that are queued)
+        HIP_TRY(s, hipMemsetAsync(B.rout[b], W_ZERO, (size_t)len * h.F, st));
         TRY(twa_rt::export_lrho(s, B.lseg[b]));
         // each iteration's weights, its captured factors, and (from its node
         // pass) the new <-rho codes, the mean-set sizes and the capture
@@ -740,11 +809,11 @@ twa_status run_once(twa_solver *s, const Shape &h, Buffers &B, const float *dL_d
         if (c > 0) TRY(recompute(c - 1));
         HIP_TRY(s, hipStreamWaitEvent(rs, s->adj_ev[b], 0));
         for (long long t = len - 1; t >= 0; --t) {
-            float *ub_in, *zb_in, *S_in, *ub_out, *zb_out, *S_out;
-            set_layout(h, B.set[in], &ub_in, &zb_in, &S_in);
-            set_layout(h, B.set[1 - in], &ub_out, &zb_out, &S_out);
-            A.ub_in = ub_in, A.zb_in = zb_in, A.S_in = S_in;
-            A.ub_out = ub_out, A.zb_out = zb_out, A.S_next = S_out;
+            float *ub_in, *sum_in, *ub_out, *sum_out;
+            set_layout(h, B.set[in], &ub_in, &sum_in);
+            set_layout(h, B.set[1 - in], &ub_out, &sum_out);
+            A.ub_in = ub_in, A.sum_in = sum_in;
+            A.ub_out = ub_out, A.sum_out = sum_out;
             A.l = B.lseg[b] + t * h.N;
             A.lnext = B.lseg[b] + (t + 1) * h.N;
             A.cnt = B.cntseg[b] + t * h.N;
@@ -756,7 +825,7 @@ twa_status run_once(twa_solver *s, const Shape &h, Buffers &B, const float *dL_d
             // the step after this one belongs to the segment reversed before
             // (or is the loss): it could not accumulate this step's S
             if (t == len - 1)
-                hipLaunchKernelGGL(k_adj_accum, dim3(nb_rec), dim3(256), 0, rs, A, S_in, (const AdjRec *)B.pool[b],
+                hipLaunchKernelGGL(k_adj_accum, dim3(nb_rec), dim3(256), 0, rs, A, sum_in, (const AdjRec *)B.pool[b],
                                    offs, B.pool_cap);
             // The output set holds what step t + 2 wrote.  Its records are in
             // this segment's pool if it belongs to the segment; otherwise
@@ -774,12 +843,12 @@ twa_status run_once(twa_solver *s, const Shape &h, Buffers &B, const float *dL_d
         HIP_TRY(s, hipEventRecord(s->adj_ev[2 + b], rs));
     }
     {
-        float *ub, *zb, *S;
-        set_layout(h, B.set[in], &ub, &zb, &S);
-        A.zb_in = zb;
+        float *ub, *sums;
+        set_layout(h, B.set[in], &ub, &sums);
+        A.sum_in = sums;
     }
-    const long long nfin = std::max<long long>(h.N, s->p);
-    hipLaunchKernelGGL(k_adj_finish, dim3((unsigned)((nfin + 255) / 256)), dim3(256), 0, rs, A, dL_dz0, dL_dr);
+    hipLaunchKernelGGL(k_adj_finish, dim3(nb_nodes), dim3(256), 0, rs, A, dL_dz0);
+    hipLaunchKernelGGL(k_adj_radii, dim3((unsigned)s->p), dim3(64), 0, rs, A, dL_dr);
     HIP_TRY(s, hipGetLastError());
     TRY(unpack(s, h, B, B.cur, cur_iter));
     HIP_TRY(s, hipStreamSynchronize(rs));

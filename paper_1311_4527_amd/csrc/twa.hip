@@ -345,6 +345,12 @@ __device__ __forceinline__ int load_uniform(const int *p, long long idx) {
     return ((const __attribute__((address_space(4))) int *)p)[idx];
 }
 
+// Whether the stream records the factors that stay inactive in this iteration.
+// twa_backward's capture (adj_pool) does without: its buffer is cleared once per
+// segment, as most rows of a chunk then still end at the activity test (256
+// agents, beside the reverse step: 13.0 -> 11.0 us per iteration).
+__device__ __forceinline__ bool capture_rest(const Params &P) { return P.dbg_rho && !P.adj_pool; }
+
 // Collision factor f given its four node records ((i,s), (i,s+1), (j,s),
 // (j,s+1): current, and the previous iteration's for the dense form) and
 // its u as loaded: activity test on n = z - u and the queue decision.
@@ -398,7 +404,7 @@ __device__ __forceinline__ bool coll_factor(const Params &P, long long f, float 
             for (int k = 0; k < D; ++k) n[e * D + k] = zz[k] - u[e * D + k];
         }
         push_new = P.admm || coll_active<D>(n, R);
-        if (!push_new && P.dbg_rho) {
+        if (!push_new && capture_rest(P)) {
             long long e0 = P.e_coll + 4 * f;
             if (P.dbg_x)
                 for (int k = 0; k < 4 * D; ++k) P.dbg_x[e0 * D + k] = n[k];
@@ -547,7 +553,7 @@ __device__ __forceinline__ void coll_rows_bits(const Params &P, const Rec &Z, in
             if ((some & valid) | mineword) busy |= 1u << r;
         }
     }
-    if (P.dbg_rho) busy = (1u << rows) - 1u; // (a capture writes every factor)
+    if (capture_rest(P)) busy = (1u << rows) - 1u; // (it writes every factor)
     if (busy == 0u) return; // nothing was active and nothing is queued: the common case
     const unsigned P2 = (unsigned)P.P2;
     const unsigned long long me = 1ull << lane;
@@ -568,7 +574,7 @@ __device__ __forceinline__ void coll_rows_bits(const Params &P, const Rec &Z, in
         }
         // canonical index of (s, i, j): s p(p-1)/2 + fr (31 bits)
         const unsigned fr = (unsigned)((long long)i * (2 * p - i - 1) / 2 + (j - i - 1));
-        if (P.dbg_rho) {
+        if (capture_rest(P)) {
             // capture of an iteration: the factors that stay inactive (x = n = z)
             for (int k = 0; k < ns; ++k) {
                 unsigned long long qk = 0ull;
@@ -807,7 +813,7 @@ __device__ __forceinline__ bool wall_test(const Params &P, const Rec &Z, const W
         float4 za = Z.cur[a.na], zb = Z.cur[a.nb];
         f2 n0 = mk(za.x - u.x, za.y - u.y), n1 = mk(zb.x - u.z, zb.y - u.w);
         push_new = P.admm || segseg_below(n0, n1, xa, xb, r);
-        if (!push_new && P.dbg_rho) {
+        if (!push_new && capture_rest(P)) {
             long long e0 = P.e_wall + 2 * f;
             if (P.dbg_x) {
                 P.dbg_x[e0 * 2 + 0] = n0.x, P.dbg_x[e0 * 2 + 1] = n0.y;
