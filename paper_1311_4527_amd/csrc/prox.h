@@ -29,6 +29,43 @@ namespace twa {
 
 TWA_HD float inv_sqrt(float x) { return 1.0f / sqrtf(x); }
 
+// Correctly rounded quotients and roots of operands far from the ends of the
+// exponent range, from an estimate within an ulp: the steps of the compiler's own
+// division and root without the scaling and the special cases around them, and
+// with one reciprocal for all quotients by the same d.  For |n| and d in
+// [2^-100, 2^80] with n / d in [2^-100, 2^100], and x in [2^-90, 2^90]: no step
+// over- or underflows, every remainder is exact, and the result is n / d and
+// sqrtf(x) to the last bit.  (The one exception: d of all ones and n a power of
+// two want the correctly rounded estimate.  v_rcp_f32 gives it: on the device,
+// every mantissa of d and of x, 10^10 quotients, none differs from n / d.)
+TWA_HD float refined_rcp(float d, float r0) { return fmaf(fmaf(-d, r0, 1.f), r0, r0); }
+TWA_HD float quotient(float n, float d, float r) {
+    float q = n * r;
+    q = fmaf(fmaf(-d, q, n), r, q);
+    return fmaf(fmaf(-d, q, n), r, q);
+}
+TWA_HD float rounded_root(float x, float s0) {
+    int i;
+    __builtin_memcpy(&i, &s0, 4);
+    const int id = i - 1, iu = i + 1;
+    float dn, up;
+    __builtin_memcpy(&dn, &id, 4);
+    __builtin_memcpy(&up, &iu, 4);
+    float s = s0;
+    if (fmaf(-dn, s0, x) <= 0.f) s = dn;
+    if (fmaf(-up, s0, x) > 0.f) s = up;
+    return s;
+}
+#ifdef __HIP_DEVICE_COMPILE__
+TWA_HD float rcp_of(float d) { return refined_rcp(d, __builtin_amdgcn_rcpf(d)); }
+TWA_HD float root_of(float x) { return rounded_root(x, __builtin_amdgcn_sqrtf(x)); }
+TWA_HD bool all_lanes(bool v) { return __builtin_amdgcn_ballot_w64(!v) == 0ull; }
+#else
+TWA_HD float rcp_of(float d) { return refined_rcp(d, 1.f / d); }
+TWA_HD float root_of(float x) { return rounded_root(x, sqrtf(x)); }
+TWA_HD bool all_lanes(bool v) { return v; }
+#endif
+
 enum : int { W_ZERO = 0, W_STD = 1, W_INF = 2 };
 
 struct f2 {
@@ -243,32 +280,74 @@ TWA_HD int trs_global(const Eig2 &g, f2 *out, f2 *alt) {
         float ta = fabsf(b1) * inv_sqrt(1.f - q * q);
         if (ta > lo && ta < hi) t = ta;
     }
-    for (int it = 0; it < 60; ++it) {
-        float y1 = b1 / t, y2 = b2 / (t + gap);
-        float S = y1 * y1 + y2 * y2;
-        float rs = inv_sqrt(S);
-        float h = rs - 1.f; // increasing in t; root where h == 0
-        if (h > 0.f) hi = t;
-        else lo = t;
-        if (fabsf(h) <= 2.4e-7f) break;
-        float dS = y1 * y1 / t + y2 * y2 / (t + gap); // = -S'/2
-        float hp = rs * rs * rs * dS;
-        float tn = t - h / hp;
-        if (!(tn > lo && tn < hi)) tn = lo > 0.f ? sqrtf(lo * hi) : 0.5f * hi;
-        if (tn == t) break;
-        t = tn;
+    // The loop is most of a minimiser, and its six divisions and the root most of
+    // the loop.  t stays in [lo, bn] and t + gap >= bn - or so, hence under this
+    // condition every operand below is in quotient()'s range: b / t and b / (t + gap)
+    // in [2^-42, 2], S in [2^-84, 4], S / t in [2^-95, 2^32], h / hp within
+    // 2^+-95.
+    // (100 agents 11.2 -> 10.8 us per iteration, 64 agents 8.8 -> 8.4, ADMM of 32
+    // agents 10.8 -> 10.5.)
+    float y1, y2, rs;
+    bool fresh = false; // y1, y2, rs are of the final t
+    const float least = 9.313225746e-10f, most = 1024.f; // 2^-30, 2^10
+    if (all_lanes(fabsf(b1) >= least && fabsf(b2) >= least && bn <= most && gap <= most)) {
+        for (int it = 0; it < 60; ++it) {
+            const float tg = t + gap, r1 = rcp_of(t), r2 = rcp_of(tg);
+            y1 = quotient(b1, t, r1), y2 = quotient(b2, tg, r2);
+            float S = y1 * y1 + y2 * y2;
+            const float root = root_of(S);
+            rs = quotient(1.f, root, rcp_of(root));
+            float h = rs - 1.f; // increasing in t; root where h == 0
+            if (h > 0.f) hi = t;
+            else lo = t;
+            if (fabsf(h) <= 2.4e-7f) {
+                fresh = true;
+                break;
+            }
+            float dS = quotient(y1 * y1, t, r1) + quotient(y2 * y2, tg, r2); // = -S'/2
+            float hp = rs * rs * rs * dS;
+            float tn = t - quotient(h, hp, rcp_of(hp));
+            if (!(tn > lo && tn < hi)) tn = lo > 0.f ? sqrtf(lo * hi) : 0.5f * hi;
+            if (tn == t) {
+                fresh = true;
+                break;
+            }
+            t = tn;
+        }
+    } else {
+        for (int it = 0; it < 60; ++it) {
+            y1 = b1 / t, y2 = b2 / (t + gap);
+            float S = y1 * y1 + y2 * y2;
+            rs = inv_sqrt(S);
+            float h = rs - 1.f;
+            if (h > 0.f) hi = t;
+            else lo = t;
+            if (fabsf(h) <= 2.4e-7f) {
+                fresh = true;
+                break;
+            }
+            float dS = y1 * y1 / t + y2 * y2 / (t + gap);
+            float hp = rs * rs * rs * dS;
+            float tn = t - h / hp;
+            if (!(tn > lo && tn < hi)) tn = lo > 0.f ? sqrtf(lo * hi) : 0.5f * hi;
+            if (tn == t) {
+                fresh = true;
+                break;
+            }
+            t = tn;
+        }
     }
-    float y1, y2;
     bool hard = t <= 1e-6f * (bn + gap);
     if (hard) {
         y2 = fminf(fmaxf(b2 / (t + gap), -1.f), 1.f);
         y1 = sqrtf(fmaxf(0.f, 1.f - y2 * y2));
         if (b1 < 0.f) y1 = -y1;
-    } else {
+        fresh = false;
+    } else if (!fresh) {
         y1 = b1 / t;
         y2 = b2 / (t + gap);
     }
-    float inv = inv_sqrt(y1 * y1 + y2 * y2);
+    const float inv = fresh ? rs : inv_sqrt(y1 * y1 + y2 * y2);
     y1 *= inv;
     y2 *= inv;
     out[0] = add(scl(g.v1, y1), scl(g.v2, y2));
@@ -409,15 +488,6 @@ TWA_HD void disk_prox(f2 m0, f2 m1, float w0, float w1, int k0, int k1, float R,
     Eig2 g = piece_quadratic(m0, m1, w0, w1, R);
     f2 best = mk(1.f, 0.f);
     int bk = CH_NONE;
-    float bF = INFINITY;
-    auto consider = [&](f2 u, int kind) {
-        float Fk = disk_F(u, m0, m1, w0, w1, R);
-        if (Fk < bF || bk == CH_NONE) {
-            bF = Fk;
-            best = u;
-            bk = kind;
-        }
-    };
     // one end pushed straight out while the other is clear: when valid it
     // is the minimiser outright (that end moves the least any feasible
     // configuration can move it, the other not at all), taken without
@@ -427,17 +497,17 @@ TWA_HD void disk_prox(f2 m0, f2 m1, float w0, float w1, int k0, int k1, float R,
     float q0 = dot(m0, m0), q1 = dot(m1, m1);
     if (q0 > 0.f && q0 < R * R) {
         f2 u = scl(m0, inv_sqrt(q0));
-        if (dot(m1, u) >= R) consider(u, CH_R0);
+        if (dot(m1, u) >= R) best = u, bk = CH_R0;
     }
     if (bk == CH_NONE && q1 > 0.f && q1 < R * R) {
         f2 u = scl(m1, inv_sqrt(q1));
-        if (dot(m0, u) >= R) consider(u, CH_R1);
+        if (dot(m0, u) >= R) best = u, bk = CH_R1;
     }
     if (bk == CH_NONE) {
         f2 t0, alt;
         int nt = trs_global(g, &t0, &alt);
-        consider(t0, CH_T);
-        if (nt == 2) consider(alt, CH_T);
+        best = t0, bk = CH_T;
+        if (nt == 2 && disk_F(alt, m0, m1, w0, w1, R) < disk_F(t0, m0, m1, w0, w1, R)) best = alt;
     }
     v0 = add(m0, scl(best, pos(R - dot(m0, best))));
     v1 = add(m1, scl(best, pos(R - dot(m1, best))));
