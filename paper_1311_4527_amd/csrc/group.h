@@ -609,7 +609,7 @@ __device__ __forceinline__ void group_run(Params P, const GroupArgs &A, char *ld
                                 if (aw) atomicOr(&wbit[lf >> 5], 1u << (lf & 31));
                             }
                         }
-                        if (nq >= kGroupSums) contribute_wave<true>(P, out, D);
+                        if ((k < kc ? nq : 2 * nqw) >= kGroupSums) contribute_wave<true>(P, out, D);
                         else contribute_wave<false>(P, out, D);
                         if (last) {
                             const int a = __popcll(__ballot(ac)), w = __popcll(__ballot(aw));

@@ -48,7 +48,7 @@ struct Params {
     unsigned long long *bits_coll;      // [nch] activity of each collision chunk's pairs
     unsigned *bits_wall;                // [Fw / 32] activity of wall factors
     const unsigned long long *chunk_coll; // [cps] (i, 64 J) of each chunk of an interval, packed 24|24 bits
-    const unsigned long long *walk_coll;  // [nwalk] (i0, J) of the activity-bit stream's tasks, packed 24|24 bits
+    const unsigned long long *walk_coll;  // [nwalk] the stream's tasks, packed: (rows, i0, J), or dense (i, j0)
     long long nwalk;
     const int *rowchunk;                // [p] chunk J of row i is rowchunk[i] + J within a break-point interval
     long long nch, cps, P2;             // chunks, chunks per interval, pairs p(p-1)/2

@@ -108,6 +108,7 @@ constexpr int kShards = 32;
 // together (coll_rows_bits); 1024 / 2048 agents and 32 walls: 2 rows 14.8 / 45.6
 // us, 4 rows 14.0 / 40.7, 6 rows 14.5 / 39.3.
 constexpr int kRows = 4;
+constexpr long long kWalkWaves = 8192; // see the walk in twa_create
 constexpr int kQueueStride = 64;
 
 enum Mode : int { M_FIRST = 0, M_FUSED = 1, M_FINAL = 2 };
@@ -621,8 +622,9 @@ __device__ __forceinline__ void coll_column(const Params &P, const Rec &Z, int c
     constexpr bool need_u = DENSE || MODE == M_FIRST;
     constexpr bool need_word = !DENSE && MODE != M_FIRST;
     const int cu = __builtin_amdgcn_readfirstlane(col);
-    const unsigned long long pk = load_uniform(P.chunk_coll, cu);
-    const int i = (int)(pk >> 24), j0 = (int)(pk & 0xffffffull);
+    // (the dense stream has its own chunks: see the walk in twa_create)
+    const unsigned long long pk = load_uniform(DENSE && SCALAR_I ? P.walk_coll : P.chunk_coll, cu);
+    const int i = (int)((pk >> 24) & 0xffffffull), j0 = (int)(pk & 0xffffffull);
     if constexpr (!DENSE && MODE == M_FUSED) {
         coll_rows_bits<D, CPW, 1>(P, Z, i, i + 1, j0 >> 6, s0, s1 - s0, lane, clear_bits, qs, qlen);
         return;
@@ -1267,7 +1269,7 @@ __device__ __forceinline__ void stream_block(const Params &P, long long b) {
         // intervals); consecutive waves take consecutive ones of the same
         // intervals
         const unsigned wave = (unsigned)b * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const unsigned per = (unsigned)(DENSE ? P.cps : P.nwalk);
+        const unsigned per = (unsigned)P.nwalk;
         const int at = (int)(wave % per), s0 = (int)(wave / per) * CPW;
         const int shard = (int)(wave % kShards), lane = threadIdx.x & 63;
         unsigned *qs = P.qc + (long long)shard * P.qcap;
@@ -1278,7 +1280,8 @@ __device__ __forceinline__ void stream_block(const Params &P, long long b) {
                 coll_column<D, MODE, CPW, true, true>(P, Z, at, s0, s1, lane, clear_bits, qs, qlen);
             } else {
                 const unsigned long long pk = load_uniform(P.walk_coll, at);
-                const int i0 = (int)(pk >> 24), J = (int)(pk & 0xffffffull), i1 = min(i0 + kRows, P.p - 1);
+                const int i0 = (int)((pk >> 24) & 0xffffffull), J = (int)(pk & 0xffffffull),
+                          i1 = min(i0 + (int)(pk >> 48), P.p - 1);
                 if constexpr (MODE == M_FUSED) {
                     // (up to half the intervals left: the half-length form)
                     if (s1 - s0 <= CPW / 2)
@@ -2898,17 +2901,29 @@ twa_status twa_create(int p, int eta, int dim, const float *radii, const float *
             for (int J = (i + 1) >> 6; J <= (p - 1) >> 6; ++J, ++c)
                 hchunk[c] = ((unsigned long long)i << 24) | (unsigned long long)(64 * J);
     }
-    // the walk of the activity-bit stream: (i0, J) for rows i0 .. i0 + kRows - 1
-    // over a chunk column J, J by J (neighbouring waves then read the same
-    // agents j)
+    // The walk of the stream.  Activity bits: (rows, i0, J) for rows i0 .. i0 +
+    // rows - 1 of a chunk column J, J by J (neighbouring waves then read the same
+    // agents j).  Four rows a wave issue least, but a launch of few waves lasts as
+    // long as one of them: fewer rows while that makes at most kWalkWaves waves
+    // (525 agents, 14 intervals, 100 iterations: one row 2.28 ms, four 2.61; a
+    // training step of 5 agents 6.46 against 7.02).  Dense: chunks (i, j0) from j = i + 1 on, which are fewer than those
+    // cut at multiples of 64 (110 agents: 155 against 172).
+    const bool dense_walk = (flags & (TWA_F_DENSE | TWA_F_ADMM)) != 0;
+    const long long blocks_s = (eta + P.cpw - 1) / P.cpw;
     std::vector<unsigned long long> hwalk;
-    for (int J = 0; J <= (p - 1) >> 6 && p > 1; ++J)
-        for (int i0 = 0; i0 + 1 < p && ((i0 + 1) >> 6) <= J; i0 += kRows)
-            hwalk.push_back(((unsigned long long)i0 << 24) | (unsigned long long)J);
+    int rows = dense_walk ? 1 : kRows;
+    if (dense_walk) {
+        for (int i = 0; i + 1 < p; ++i)
+            for (int j0 = i + 1; j0 < p; j0 += 64) hwalk.push_back(((unsigned long long)i << 24) | (unsigned long long)j0);
+    } else {
+        while (rows > 1 && (P.cps * blocks_s) / (rows / 2) <= kWalkWaves) rows /= 2;
+        for (int J = 0; J <= (p - 1) >> 6 && p > 1; ++J)
+            for (int i0 = 0; i0 + 1 < p && ((i0 + 1) >> 6) <= J; i0 += rows)
+                hwalk.push_back(((unsigned long long)rows << 48) | ((unsigned long long)i0 << 24) | (unsigned long long)J);
+    }
     P.nwalk = (long long)hwalk.size();
     if (hwalk.empty()) hwalk.push_back(0ull);
-    const long long walk = (flags & (TWA_F_DENSE | TWA_F_ADMM)) ? P.cps : P.nwalk;
-    P.nbc = (walk * ((eta + P.cpw - 1) / P.cpw) + kBlock / 64 - 1) / (kBlock / 64);
+    P.nbc = (P.nwalk * blocks_s + kBlock / 64 - 1) / (kBlock / 64);
     P.nbw = (Fw + kBlock - 1) / kBlock;
     P.nbe = (Fe + kBlock - 1) / kBlock;
     P.nbf = (Ff + kBlock - 1) / kBlock;
@@ -2916,8 +2931,8 @@ twa_status twa_create(int p, int eta, int dim, const float *radii, const float *
     s->nblocks_queue = 4096;
     {
         // a shard takes the appends of every kShards-th wave of the column walk
-        long long waves = walk * ((eta + P.cpw - 1) / P.cpw);
-        P.qcap = (waves + kShards - 1) / kShards * 64 * P.cpw * (walk == P.cps ? 1 : kRows);
+        long long waves = P.nwalk * blocks_s;
+        P.qcap = (waves + kShards - 1) / kShards * 64 * P.cpw * rows;
     }
     P.e_energy = Ff;
     P.e_coll = Ff + 2 * Fe;
