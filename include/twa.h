@@ -22,7 +22,10 @@
  *     On failure twa_last_error() describes the cause.  A device error
  *     (TWA_E_DEVICE) latches: every later call on that solver fails with it.
  *   - Calls are asynchronous on the stream unless stated; calls on one
- *     solver must not overlap (one host thread at a time).
+ *     solver must not overlap (one host thread at a time).  A failure on the
+ *     device that a queued call cannot report (a workgroup that waits in
+ *     vain for another) makes the positions read back afterwards NaN, and
+ *     the next call that synchronises returns TWA_E_DEVICE.
  *
  * Canonical edge order (used by state get/set and the per-edge debug output;
  * factor order is the same with one entry per factor):

@@ -711,7 +711,9 @@ twa_status run_once(twa_solver *s, const Shape &h, Buffers &B, const float *dL_d
         }
     }
     HIP_TRY(s, hipMemcpyAsync(&used, B.arena_cursor, sizeof(unsigned), hipMemcpyDeviceToHost, st));
+    TRY(twa_rt::group_flags(s, s->adj_used + 2)); // (the segments below run in plain launches)
     HIP_TRY(s, hipStreamSynchronize(st));
+    if (s->adj_used[2] || s->adj_used[3]) return twa_rt::group_lost(s);
     if (used > B.arena_cap) {
         *outcome = kArenaFull;
         *need = used;
@@ -998,7 +1000,7 @@ twa_status tape_setup(twa_solver *s) {
             ev = nullptr;
             return fail(s, TWA_E_DEVICE, "hipEventCreate failed");
         }
-    if (hipHostMalloc(reinterpret_cast<void **>(&s->adj_used), 2 * sizeof(unsigned), hipHostMallocDefault) !=
+    if (hipHostMalloc(reinterpret_cast<void **>(&s->adj_used), 4 * sizeof(unsigned), hipHostMallocDefault) !=
         hipSuccess) {
         (void)hipGetLastError();
         s->adj_used = nullptr;

@@ -81,10 +81,10 @@ struct GroupCtl {
     unsigned reg, pad0[31];  // workgroups that came; bit 31 once the group is frozen
     unsigned size, pad1[31]; // members (0 until frozen)
     unsigned bar, pad2[31];  // barrier arrivals
-    unsigned total[4];       // last iteration: active collision, active wall, queued factors
-    unsigned pad3[28];
+    unsigned total[3];       // last iteration: active collision, active wall, queued factors
+    unsigned pad3[29];
     unsigned turn;           // buffer the next iteration adds to (kept between launches)
-    unsigned stuck;          // a wait ran out (never, short of a fault): results invalid
+    unsigned stuck;          // a wait ran out (never, short of a fault): results invalid from here on
 };
 
 // byte offsets in the dynamic LDS
@@ -111,15 +111,23 @@ __device__ __forceinline__ unsigned agent_load(const unsigned *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// a wait gives up after about this many polls (seconds): a member that left
-// abnormally must not hang the device
-constexpr unsigned kGroupPatience = 1u << 25;
+// A wait gives up after this many polls (ten seconds or so): a member that
+// left abnormally must not hang the device.  The first one to give up says so
+// in `stuck`, which every wait looks at now and then: the rest of the launch
+// ends without waiting that long again, and later launches end at once.  What
+// the solver holds is invalid from then on, and whatever reads it says so
+// (GaveUp).
+constexpr unsigned kGroupPatience = 1u << 24;
+
+__device__ __forceinline__ void group_give_up(GroupCtl *c) {
+    __hip_atomic_store(&c->stuck, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Join the group: members get their rank in *rank and the member count in
-// *size; false for a workgroup that came too late.
+// *size; false for a workgroup that came too late, or where a wait ran out.
 __device__ __forceinline__ bool group_join(GroupCtl *c, int want, unsigned *rank, unsigned *size) {
-    const unsigned r = atomicAdd(&c->reg, 1u);
-    if (r & kGroupFrozen) return false;
+    const unsigned stuck = agent_load(&c->stuck), r = atomicAdd(&c->reg, 1u);
+    if (stuck || (r & kGroupFrozen)) return false;
     if (r == 0u) {
         // about 50 us for the rest of the launch to arrive
         for (int n = 0; n < 128 && agent_load(&c->reg) < (unsigned)want; ++n) __builtin_amdgcn_s_sleep(1);
@@ -129,7 +137,7 @@ __device__ __forceinline__ bool group_join(GroupCtl *c, int want, unsigned *rank
     } else {
         unsigned m = 0u;
         for (unsigned n = 0; n < kGroupPatience && (m = agent_load(&c->size)) == 0u; ++n) __builtin_amdgcn_s_sleep(1);
-        if (m == 0u) c->stuck = 1u;
+        if (m == 0u) group_give_up(c);
         *size = m;
     }
     *rank = r;
@@ -137,8 +145,9 @@ __device__ __forceinline__ bool group_join(GroupCtl *c, int want, unsigned *rank
 }
 
 // Barrier `n` (1, 2, ...) of the group.  Every memory operation of the
-// workgroup's waves is complete before it arrives.
-__device__ __forceinline__ void group_barrier(GroupCtl *c, unsigned size, unsigned n) {
+// workgroup's waves is complete before it arrives.  *gone (LDS) is set where
+// the wait ran out, here or in another member.
+__device__ __forceinline__ void group_barrier(GroupCtl *c, unsigned size, unsigned n, int *gone) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -146,8 +155,9 @@ __device__ __forceinline__ void group_barrier(GroupCtl *c, unsigned size, unsign
         const unsigned all = size * n;
         unsigned k = 0;
         while (agent_load(&c->bar) < all)
-            if (++k == kGroupPatience) {
-                c->stuck = 1u;
+            if ((++k & 1023u) == 0u && (k >= kGroupPatience || agent_load(&c->stuck))) {
+                group_give_up(c);
+                *gone = 1;
                 break;
             }
     }
@@ -443,17 +453,17 @@ __device__ __forceinline__ void group_run(Params P, const GroupArgs &A, char *ld
     unsigned long long *word = reinterpret_cast<unsigned long long *>(lds + A.L.word);
     unsigned *wbit = reinterpret_cast<unsigned *>(lds + A.L.wbit);
     unsigned *q = reinterpret_cast<unsigned *>(lds + A.L.q), *qw = reinterpret_cast<unsigned *>(lds + A.L.qw);
-    __shared__ int len[2];           // queue lengths
-    __shared__ int more;             // iteration + 1: some wave has items left
-    __shared__ unsigned totals[4];   // this iteration's active and queued factors
+    // queue lengths; iteration + 1 where some wave has items left; whether a
+    // wait ran out (read together, once a round)
+    __shared__ int len[4];
+    __shared__ unsigned totals[3];   // this iteration's active and queued factors
     for (int nd = threadIdx.x; nd < N; nd += T) {
         zc[nd] = P.zr_cur[nd];
         if (DENSE) zp[nd] = P.zr_prev[nd];
     }
     for (int i = threadIdx.x; i < p; i += T) rad[i] = P.radii[i];
-    if (threadIdx.x < 2) len[threadIdx.x] = 0;
-    if (threadIdx.x == 0) more = 0;
-    if (threadIdx.x < 4) totals[threadIdx.x] = 0u;
+    if (threadIdx.x < 4) len[threadIdx.x] = 0;
+    if (threadIdx.x < 3) totals[threadIdx.x] = 0u;
     P.radii = rad;
     constexpr bool CYC = group_cyclic(T);
     constexpr int WORDS = group_words(T);
@@ -553,13 +563,14 @@ __device__ __forceinline__ void group_run(Params P, const GroupArgs &A, char *ld
                     group_push(qw, &len[1], queue, (val & kPrev) | (unsigned)lw);
                     ++wt;
                 }
-                if (l < S.nitems && lane == 0) more = it + 1;
+                if (l < S.nitems && lane == 0) len[2] = it + 1;
                 __syncthreads();
                 const int nq = len[0], nqw = len[1];
-                const bool items = more == it + 1;
+                const bool items = len[2] == it + 1, gone = len[3] != 0;
                 end = !items && wt * T >= S.nwall;
                 __syncthreads();
-                if (threadIdx.x == 0) more = 0;
+                if (gone) return; // (the same on every lane: set before the last barrier's end)
+                if (threadIdx.x == 0) len[2] = 0;
                 // (room left for another round: the minimisers wait for it)
                 if (!end && nq <= most && nqw <= group_wall_queue(T) - T) {
                     __syncthreads();
@@ -645,7 +656,7 @@ __device__ __forceinline__ void group_run(Params P, const GroupArgs &A, char *ld
             __syncthreads();
             if (threadIdx.x < 3 && totals[threadIdx.x]) atomicAdd(&A.ctl->total[threadIdx.x], totals[threadIdx.x]);
         }
-        group_barrier(A.ctl, size, (unsigned)it + 1u);
+        group_barrier(A.ctl, size, (unsigned)it + 1u, &len[3]);
         if (threadIdx.x == 0) totals[2] = 0u;
         group_nodes<D, DENSE, T>(P, A, b, zc, zp, last ? n0 : 0, last ? n1 : 0);
         __syncthreads();
@@ -655,7 +666,7 @@ __device__ __forceinline__ void group_run(Params P, const GroupArgs &A, char *ld
     const long long c0 = P.nch * rank / size, c1 = P.nch * (rank + 1) / size;
     for (long long w = c0 + threadIdx.x; w < c1; w += T)
         __hip_atomic_store(&P.bits_coll[w], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    group_barrier(A.ctl, size, (unsigned)A.K + 1u);
+    group_barrier(A.ctl, size, (unsigned)A.K + 1u, &len[3]);
     for (int sh = (int)rank; sh < A.want; sh += (int)size) {
         if (many) {
             S.take(P, A.want, sh, nitems_all);
@@ -766,5 +777,5 @@ __global__ void k_group_arm(GroupCtl *c, int n) {
     const int g = (int)blockIdx.x * (int)(blockDim.x / 4) + (int)(threadIdx.x >> 2), k = (int)(threadIdx.x & 3);
     if (g >= n) return;
     if (k == 0) c[g].reg = c[g].size = c[g].bar = 0u;
-    c[g].total[k] = 0u;
+    if (k < 3) c[g].total[k] = 0u;
 }

@@ -133,7 +133,7 @@ struct twa_solver {
     hipStream_t stream = nullptr;
     twa_rt::Params P{};
     int *stats_dev = nullptr;
-    double *quality_dev = nullptr; // twa_get_quality: objective, largest move, clearance key
+    double *quality_dev = nullptr; // twa_get_quality: objective, largest move, clearance key, whether a group gave up
     unsigned *resid_dev = nullptr;  // residual of the last finalized iteration (float bits)
     bool resid_valid = false;       // resid_dev holds the last iteration's residual
     int *bad_dev = nullptr;
@@ -226,7 +226,8 @@ struct twa_solver {
         void *mem = nullptr;
         size_t bytes = 0;
     } tape;
-    unsigned *adj_used = nullptr; // pinned host [2]: records each recompute wanted
+    // pinned host [4]: records each recompute wanted; whether a group gave up
+    unsigned *adj_used = nullptr;
 };
 
 namespace twa_rt {
@@ -256,6 +257,10 @@ twa_status tape_take(twa_solver *s);
 // TWA_F_TAPE at create: look up the static scratch of twa_backward_noalloc
 // on the solver's device, make twa_backward's second stream and its events
 twa_status tape_setup(twa_solver *s);
+// queue the copy of the solver's two words that say whether a wait inside a
+// group ran out; the error of a call that finds one set
+twa_status group_flags(twa_solver *s, unsigned *to);
+twa_status group_lost(twa_solver *s);
 
 } // namespace twa_rt
 

@@ -1901,6 +1901,13 @@ __global__ __launch_bounds__(kBlock) void kp_nodes(const Params *insts, const in
     else nodes_block<3>(P, m.y);
 }
 
+// Whether a wait inside one of a solver's groups ran out (GroupCtl::stuck of
+// its own group and of its group in a batch; null: none).
+struct GaveUp {
+    const unsigned *own = nullptr, *batch = nullptr;
+    __device__ __forceinline__ bool any() const { return (own && *own) || (batch && *batch); }
+};
+
 // ------------------------------------------------------------------ layout conversion
 // canonical [p][eta+1][dim] <-> time-major node records
 __global__ void k_z_import(float4 *zr, const float *z, int p, int eta, int D, const unsigned char *lrho, int keep_w,
@@ -1918,12 +1925,15 @@ __global__ void k_z_import(float4 *zr, const float *z, int p, int eta, int D, co
     else if (!keep_w) r.w = (float)(s == 0 ? startcode : (s == eta ? goalcode : W_STD));
     zr[nd] = r;
 }
-__global__ void k_z_export(const float4 *zr, float *z, unsigned char *lrho, int p, int eta, int D) {
+// (NaN where a group gave up: what it left is no plan, and this call does not
+// wait for the device to say so)
+__global__ void k_z_export(const float4 *zr, float *z, unsigned char *lrho, int p, int eta, int D, GaveUp lost) {
     long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     long long N = (long long)p * (eta + 1);
     if (t >= N) return;
     int i = (int)(t / (eta + 1)), s = (int)(t % (eta + 1));
     float4 r = zr[(long long)s * p + i];
+    if (lost.any()) r.x = r.y = r.z = NAN;
     if (z) {
         z[t * D + 0] = r.x;
         z[t * D + 1] = r.y;
@@ -1949,7 +1959,8 @@ __device__ __forceinline__ unsigned long long order_key(double v) {
 // one workgroup of 1024 lanes: objective and largest move, reduced in a
 // fixed order; also arms the clearance minimum for k_quality_clearance
 __global__ __launch_bounds__(1024) void k_quality_sums(const float4 *zr, const float4 *zp, const float *C, int p,
-                                                       int eta, double *out, unsigned long long *min_key) {
+                                                       int eta, double *out, unsigned long long *min_key,
+                                                       GaveUp lost) {
     __shared__ double part[2][1024];
     double obj = 0.0, mv = 0.0;
     const long long S = (long long)p * eta, N = (long long)p * (eta + 1);
@@ -1977,6 +1988,7 @@ __global__ __launch_bounds__(1024) void k_quality_sums(const float4 *zr, const f
     if (threadIdx.x == 0) {
         out[0] = part[0][0];
         out[1] = part[1][0];
+        out[3] = lost.any() ? 1.0 : 0.0;
         *min_key = order_key(INFINITY);
     }
 }
@@ -2049,8 +2061,10 @@ __global__ void k_fill_bits(unsigned *bits, long long nwords, unsigned v) {
     long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t < nwords) bits[t] = v;
 }
-__global__ void k_finite(const float4 *zr, long long N, const float *u, long long nu, int *bad) {
+// *bad: 1 where a value is not finite, 2 where a group gave up
+__global__ void k_finite(const float4 *zr, long long N, const float *u, long long nu, int *bad, GaveUp lost) {
     long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t == 0 && lost.any()) atomicOr(bad, 2);
     if (t < N) {
         float4 r = zr[t];
         if (!isfinite(r.x) || !isfinite(r.y) || !isfinite(r.z)) atomicOr(bad, 1);
@@ -2391,16 +2405,13 @@ twa_status prepare_group(twa_solver *s) {
 
 constexpr int kGroupChunk = 1024; // iterations per launch at most
 
-// whether a wait inside a group ever ran out (copied behind the stream's work)
-twa_status group_stuck(twa_solver *s, unsigned (&stuck)[2]) {
-    const void *ctl[2] = {s->group_ctl, s->batch_ctl};
-    for (int k = 0; k < 2; ++k) {
-        stuck[k] = 0;
-        if (ctl[k])
-            HIP_TRY(s, hipMemcpyAsync(&stuck[k], &static_cast<const GroupCtl *>(ctl[k])->stuck, sizeof(unsigned),
-                                      hipMemcpyDeviceToHost, s->stream));
-    }
-    return TWA_OK;
+// where this solver's groups (its own, and the one in its batch) say that a
+// wait ran out
+GaveUp gave_up(const twa_solver *s) {
+    GaveUp g;
+    if (s->group_ctl) g.own = &static_cast<const GroupCtl *>(s->group_ctl)->stuck;
+    if (s->batch_ctl) g.batch = &static_cast<const GroupCtl *>(s->batch_ctl)->stuck;
+    return g;
 }
 
 // k iterations of a mid-sized instance at the steady rho0, a u update
@@ -2541,7 +2552,7 @@ twa_status reset_state_buffers(twa_solver *s) {
 }
 
 // canonical z, u, <-rho of a state without a pending u update
-__global__ void k_z_export(const float4 *zr, float *z, unsigned char *lrho, int p, int eta, int D);
+__global__ void k_z_export(const float4 *zr, float *z, unsigned char *lrho, int p, int eta, int D, GaveUp lost);
 __global__ void k_u_convert(Params P, float *u, int D, int dir);
 
 // TWA_F_TAPE: remember the current (settled) state as the start of the
@@ -2550,7 +2561,7 @@ twa_status save_origin(twa_solver *s) {
     if (!(s->flags & TWA_F_TAPE)) return TWA_OK;
     unsigned nb = (unsigned)((s->P.N + 255) / 256);
     hipLaunchKernelGGL(k_z_export, dim3(nb), dim3(256), 0, s->stream, (const float4 *)s->P.zr_cur, s->origin_z,
-                       s->origin_l, s->p, s->eta, s->dim);
+                       s->origin_l, s->p, s->eta, s->dim, gave_up(s));
     long long E = s->P.e_wall + 2 * s->P.Fw;
     hipLaunchKernelGGL(k_u_convert, dim3((unsigned)((E + 255) / 256)), dim3(256), 0, s->stream, s->P, s->origin_u,
                        s->dim, 1);
@@ -2732,9 +2743,23 @@ twa_status run_segment(twa_solver *s, long long len, const SegCapture &c, int sl
 twa_status export_lrho(twa_solver *s, unsigned char *lrho) {
     unsigned nb = (unsigned)((s->P.N + 255) / 256);
     hipLaunchKernelGGL(k_z_export, dim3(nb), dim3(256), 0, s->stream, (const float4 *)s->P.zr_cur, (float *)nullptr,
-                       lrho, s->p, s->eta, s->dim);
+                       lrho, s->p, s->eta, s->dim, gave_up(s));
     HIP_TRY(s, hipGetLastError());
     return TWA_OK;
+}
+
+twa_status group_flags(twa_solver *s, unsigned *to) {
+    const GaveUp g = gave_up(s);
+    const unsigned *from[2] = {g.own, g.batch};
+    for (int k = 0; k < 2; ++k) {
+        to[k] = 0;
+        if (from[k]) HIP_TRY(s, hipMemcpyAsync(to + k, from[k], sizeof(unsigned), hipMemcpyDeviceToHost, s->stream));
+    }
+    return TWA_OK;
+}
+
+twa_status group_lost(twa_solver *s) {
+    return fail(s, TWA_E_DEVICE, "a group of workgroups gave up waiting for a member");
 }
 
 } // namespace twa_rt
@@ -2974,7 +2999,7 @@ twa_status twa_create(int p, int eta, int dim, const float *radii, const float *
         dev_alloc(s, &P.x_wall, (size_t)std::max<long long>(1, Fw)) ||
         dev_alloc(s, &wbc_d, (size_t)std::max<long long>(1, (Fc + 63) / 64)) ||
         dev_alloc(s, &wbw_d, (size_t)std::max<long long>(1, (Fw + 63) / 64)) ||
-        dev_alloc(s, &s->stats_dev, 4) || dev_alloc(s, &s->bad_dev, 1) || dev_alloc(s, &s->quality_dev, 3) ||
+        dev_alloc(s, &s->stats_dev, 4) || dev_alloc(s, &s->bad_dev, 1) || dev_alloc(s, &s->quality_dev, 4) ||
         dev_alloc(s, &s->resid_dev, 1))
         return bail(TWA_E_NOMEM);
     unsigned long long *chunk_d, *walk_d;
@@ -3211,7 +3236,7 @@ twa_status twa_get_trajectories(twa_solver *s, float *z_out) {
     if (!z_out) return fail(s, TWA_E_INVALID, "null z_out");
     unsigned nb = (unsigned)((s->P.N + 255) / 256);
     hipLaunchKernelGGL(k_z_export, dim3(nb), dim3(256), 0, s->stream, (const float4 *)s->P.zr_cur, z_out,
-                       (unsigned char *)nullptr, s->p, s->eta, s->dim);
+                       (unsigned char *)nullptr, s->p, s->eta, s->dim, gave_up(s));
     HIP_TRY(s, hipGetLastError());
     return TWA_OK;
 }
@@ -3222,7 +3247,7 @@ twa_status twa_get_state(twa_solver *s, float *z, float *u, unsigned char *lrho,
     unsigned nb = (unsigned)((s->P.N + 255) / 256);
     if (z || lrho)
         hipLaunchKernelGGL(k_z_export, dim3(nb), dim3(256), 0, s->stream, (const float4 *)s->P.zr_cur, z, lrho, s->p,
-                           s->eta, s->dim);
+                           s->eta, s->dim, gave_up(s));
     if (u) {
         long long E = s->P.e_wall + 2 * s->P.Fw;
         hipLaunchKernelGGL(k_u_convert, dim3((unsigned)((E + 255) / 256)), dim3(256), 0, s->stream, s->P, u, s->dim,
@@ -3248,11 +3273,8 @@ twa_status twa_get_stats(twa_solver *s, twa_stats *out) {
     HIP_TRY(s, hipMemcpyAsync(h, s->stats_dev, sizeof(int) * 3, hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(s, hipMemcpyAsync(&r, s->resid_dev, sizeof(unsigned), hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(s, hipMemcpyAsync(&overflow, s->P.counters + 5, sizeof(int), hipMemcpyDeviceToHost, s->stream));
-    unsigned stuck[2];
-    TRY(group_stuck(s, stuck));
     double obj = 0, clr = 0;
     TRY(twa_get_quality(s, &obj, &clr, nullptr)); // synchronises
-    if (stuck[0] || stuck[1]) return fail(s, TWA_E_DEVICE, "a group of workgroups gave up waiting for a member");
     out->iter = s->iter;
     out->active_coll = h[0];
     out->active_wall = h[1];
@@ -3273,14 +3295,15 @@ twa_status twa_get_quality(twa_solver *s, double *objective, double *min_clearan
     const Params &P = s->P;
     unsigned long long *min_key = reinterpret_cast<unsigned long long *>(s->quality_dev + 2);
     hipLaunchKernelGGL(k_quality_sums, dim3(1), dim3(1024), 0, s->stream, (const float4 *)P.zr_cur,
-                       (const float4 *)P.zr_prev, P.C, s->p, s->eta, s->quality_dev, min_key);
+                       (const float4 *)P.zr_prev, P.C, s->p, s->eta, s->quality_dev, min_key, gave_up(s));
     const long long rows = (long long)s->p * s->eta;
     hipLaunchKernelGGL(k_quality_clearance, dim3((unsigned)std::min<long long>(rows, 8192)), dim3(256), 0, s->stream,
                        (const float4 *)P.zr_cur, P.radii, P.walls, s->p, s->eta, s->W, s->dim, min_key);
     HIP_TRY(s, hipGetLastError());
-    double h[3];
+    double h[4];
     HIP_TRY(s, hipMemcpyAsync(h, s->quality_dev, sizeof(h), hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(s, hipStreamSynchronize(s->stream));
+    if (h[3] != 0.0) return twa_rt::group_lost(s);
     unsigned long long k;
     std::memcpy(&k, &h[2], sizeof(k));
     const unsigned long long b = (k >> 63) ? (k & 0x7fffffffffffffffull) : ~k;
@@ -3307,25 +3330,37 @@ twa_status twa_sizes(const twa_solver *s, long long *n_factors, long long *n_edg
     return TWA_OK;
 }
 
+// For the tests of the error paths (not declared in the header): as if a wait
+// of this solver's group (batch: of its group in its batch) had run out in the
+// work queued so far.
+twa_status twa_debug_group_stuck(twa_solver *s, int batch) {
+    TRY(check_alive(s));
+    const GaveUp g = gave_up(s);
+    const unsigned *at = batch ? g.batch : g.own;
+    if (!at) return fail(s, TWA_E_STATE, "no group");
+    const unsigned one = 1;
+    HIP_TRY(s, hipMemcpyAsync(const_cast<unsigned *>(at), &one, sizeof(one), hipMemcpyHostToDevice, s->stream));
+    HIP_TRY(s, hipStreamSynchronize(s->stream));
+    return TWA_OK;
+}
+
 twa_status twa_check_finite(twa_solver *s) {
     TRY(check_alive(s));
     TRY(finalize(s));
     HIP_TRY(s, hipMemsetAsync(s->bad_dev, 0, sizeof(int), s->stream));
     unsigned nb = (unsigned)((s->P.N + 255) / 256);
     hipLaunchKernelGGL(k_finite, dim3(nb), dim3(256), 0, s->stream, (const float4 *)s->P.zr_cur, s->P.N,
-                       (const float *)s->P.u_coll, (long long)(4 * s->dim * s->P.Fc), s->bad_dev);
+                       (const float *)s->P.u_coll, (long long)(4 * s->dim * s->P.Fc), s->bad_dev, gave_up(s));
     hipLaunchKernelGGL(k_finite, dim3(1), dim3(256), 0, s->stream, (const float4 *)s->P.zr_cur, 0LL,
-                       (const float *)s->P.u_wall, (long long)(4 * s->P.Fw), s->bad_dev);
+                       (const float *)s->P.u_wall, (long long)(4 * s->P.Fw), s->bad_dev, GaveUp{});
     hipLaunchKernelGGL(k_finite, dim3(1), dim3(256), 0, s->stream, (const float4 *)s->P.zr_cur, 0LL,
-                       (const float *)s->P.u_energy, (long long)(2 * s->dim * s->P.Fe), s->bad_dev);
+                       (const float *)s->P.u_energy, (long long)(2 * s->dim * s->P.Fe), s->bad_dev, GaveUp{});
     HIP_TRY(s, hipGetLastError());
     int bad = 0, overflow = 0;
     HIP_TRY(s, hipMemcpyAsync(&bad, s->bad_dev, sizeof(int), hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(s, hipMemcpyAsync(&overflow, s->P.counters + 5, sizeof(int), hipMemcpyDeviceToHost, s->stream));
-    unsigned stuck[2];
-    TRY(group_stuck(s, stuck));
     HIP_TRY(s, hipStreamSynchronize(s->stream));
-    if (stuck[0] || stuck[1]) return fail(s, TWA_E_DEVICE, "a group of workgroups gave up waiting for a member");
+    if (bad & 2) return twa_rt::group_lost(s);
     if (bad) return fail(s, TWA_E_NUMERIC, "non-finite value in z or u");
     if (overflow) return fail(s, TWA_E_NUMERIC, "consensus sum beyond its fixed-point range (diverging iterates)");
     return TWA_OK;
