@@ -89,7 +89,7 @@ struct GroupCtl {
 
 // byte offsets in the dynamic LDS
 struct GroupLds {
-    unsigned zc, zp, rad, item, word, wbit, q, qw, total;
+    unsigned zc, zp, rad, item, word, wbit, q, qw;
     int items, walls32; // items and 32-factor wall units of the largest share
 };
 

@@ -2353,16 +2353,14 @@ bool group_layout(const twa_solver *s, int want, int T, GroupLds *L, unsigned *b
     // (a share queues at most all its factors)
     L->q = take(4LL * std::min<long long>(group_queue(T), (long long)L->items * group_words(T) * 64));
     L->qw = take(4LL * std::min<long long>(group_wall_queue(T), 32LL * L->walls32));
-    L->total = (unsigned)off;
     *bytes = (unsigned)off;
     return off <= (long long)kGroupLdsMax;
 }
 
 template <int D, bool DENSE>
-twa_status group_attr(twa_solver *s) {
-    HIP_TRY(s, hipFuncSetAttribute(reinterpret_cast<const void *>(k_group<D, DENSE>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGroupLdsMax));
-    return TWA_OK;
+bool group_attr() {
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(k_group<D, DENSE>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGroupLdsMax) == hipSuccess;
 }
 
 // Mid-sized instances (beyond the one-workgroup path, up to this many
@@ -2374,7 +2372,8 @@ twa_status group_attr(twa_solver *s) {
 constexpr long long kGroupFactors = 700000;
 
 // Choose the group of a mid-sized instance and allocate what its launches
-// share; leaves s->group_want 0 where the plain launches are kept.
+// share; leaves s->group_want 0 where the plain launches are kept, also where
+// there is no memory for the group (they need none).
 twa_status prepare_group(twa_solver *s) {
     const Params &P = s->P;
     if (P.Fc + P.Fw > kGroupFactors) return TWA_OK;
@@ -2387,18 +2386,32 @@ twa_status prepare_group(twa_solver *s) {
     GroupLds L;
     unsigned bytes;
     if (!group_layout(s, want, kGroupBlock, &L, &bytes)) return TWA_OK;
-    GroupCtl *ctl;
-    TRY(dev_alloc(s, &ctl, 1));
-    TRY(dev_alloc(s, &s->group_acc, (size_t)3 * s->dim * P.N));
-    TRY(dev_alloc(s, &s->group_cnt, (size_t)3 * P.N));
-    TRY(dev_alloc(s, &s->group_xe, (size_t)(P.Fe * 2 + (P.vo ? P.p : 0)) * s->dim));
-    TRY(dev_alloc(s, &s->group_sent, (size_t)P.Fe));
-    HIP_TRY(s, hipMemsetAsync(ctl, 0, sizeof(GroupCtl), s->stream));
-    HIP_TRY(s, hipMemsetAsync(s->group_acc, 0, sizeof(unsigned long long) * 3 * s->dim * P.N, s->stream));
-    HIP_TRY(s, hipMemsetAsync(s->group_cnt, 0, sizeof(int) * 3 * P.N, s->stream));
-    if (s->dim == 2) TRY(P.dense ? (group_attr<2, true>(s)) : (group_attr<2, false>(s)));
-    else TRY(P.dense ? (group_attr<3, true>(s)) : (group_attr<3, false>(s)));
-    s->group_ctl = ctl;
+    if (!(s->dim == 2 ? (P.dense ? group_attr<2, true>() : group_attr<2, false>())
+                      : (P.dense ? group_attr<3, true>() : group_attr<3, false>()))) {
+        (void)hipGetLastError();
+        return TWA_OK;
+    }
+    // one buffer: the words and sums, which start at zero, then x and sent
+    size_t off = 0;
+    auto take = [&](size_t n) {
+        const size_t at = off;
+        off += (n + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t o_ctl = take(sizeof(GroupCtl)), o_acc = take(sizeof(unsigned long long) * 3 * s->dim * P.N),
+                 o_cnt = take(sizeof(int) * 3 * P.N), zeros = off,
+                 o_xe = take(sizeof(float) * (P.Fe * 2 + (P.vo ? P.p : 0)) * s->dim), o_sent = take((size_t)P.Fe);
+    char *m;
+    if (dev_alloc(s, &m, off) != TWA_OK) {
+        s->err.clear();
+        return TWA_OK;
+    }
+    HIP_TRY(s, hipMemsetAsync(m, 0, zeros, s->stream));
+    s->group_ctl = m + o_ctl;
+    s->group_acc = reinterpret_cast<unsigned long long *>(m + o_acc);
+    s->group_cnt = reinterpret_cast<int *>(m + o_cnt);
+    s->group_xe = reinterpret_cast<float *>(m + o_xe);
+    s->group_sent = reinterpret_cast<unsigned char *>(m + o_sent);
     s->group_want = want;
     return TWA_OK;
 }
@@ -2794,9 +2807,11 @@ void twa_destroy(twa_solver *s) {
     delete s;
 }
 
-twa_status twa_create(int p, int eta, int dim, const float *radii, const float *x0, const float *xT, int n_walls,
-                      const float *walls, const float *C, float rho0, float alpha, unsigned flags,
-                      void *hip_stream, twa_solver **out) {
+// member: an instance of a batch, whose launches use none of what a solver
+// keeps for its own group
+static twa_status create_solver(int p, int eta, int dim, const float *radii, const float *x0, const float *xT,
+                                int n_walls, const float *walls, const float *C, float rho0, float alpha,
+                                unsigned flags, void *hip_stream, bool member, twa_solver **out) {
     if (!out) return TWA_E_INVALID;
     *out = nullptr;
     twa_solver *s = new (std::nothrow) twa_solver();
@@ -3077,7 +3092,7 @@ twa_status twa_create(int p, int eta, int dim, const float *radii, const float *
     if (tiny(s)) {
         const twa_status st = prepare_tiny(s);
         if (st != TWA_OK) return bail(st);
-    } else {
+    } else if (!member) {
         const twa_status st = prepare_group(s);
         if (st != TWA_OK) return bail(st);
     }
@@ -3085,6 +3100,12 @@ twa_status twa_create(int p, int eta, int dim, const float *radii, const float *
     if (hipStreamSynchronize(s->stream) != hipSuccess) return bail(TWA_E_DEVICE);
     *out = s;
     return TWA_OK;
+}
+
+twa_status twa_create(int p, int eta, int dim, const float *radii, const float *x0, const float *xT, int n_walls,
+                      const float *walls, const float *C, float rho0, float alpha, unsigned flags,
+                      void *hip_stream, twa_solver **out) {
+    return create_solver(p, eta, dim, radii, x0, xT, n_walls, walls, C, rho0, alpha, flags, hip_stream, false, out);
 }
 
 twa_status twa_set_init(twa_solver *s, const float *z) {
@@ -3464,19 +3485,24 @@ twa_status batch_bins(twa_batch *b) {
 // instances in an order that keeps a group on one XCD (blocks go to the 8 XCDs
 // in turn) and starts the large groups first.  A share has 1500 factors at
 // least, about six per lane: less and the barrier is most of the iteration.
-// Leaves n_slots 0, and the phased launches in use, where an instance does not
-// fit a workgroup's LDS, where there is no memory for the groups, and in the
+// Made when block 0 is first asked for.  Leaves n_slots 0, and the phased
+// launches in use, where an instance does not fit a workgroup's LDS, where
+// there is no memory for the groups, and in the
 // dense form: it streams u of every factor, which the phased kernel has more
 // waves in flight for (64 instances 57 us per iteration, in groups 65; 16
 // instances 26 against 42).
 twa_status batch_groups(twa_batch *b) {
+    if (b->n_slots > 0) return TWA_OK;
     const int n = (int)b->solvers.size();
     for (twa_solver *s : b->solvers)
         if (s->P.dense) return TWA_OK;
     const void *kernel = reinterpret_cast<const void *>(kp_group);
-    BHIP_TRY(b, hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGroupLdsMax));
     int cus = 0;
-    BHIP_TRY(b, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->mem.device));
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGroupLdsMax) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->mem.device) != hipSuccess) {
+        (void)hipGetLastError();
+        return TWA_OK;
+    }
     long long total = 0;
     for (twa_solver *s : b->solvers) total += s->P.Fc + s->P.Fw;
     std::vector<GroupArgs> g((size_t)n);
@@ -3498,7 +3524,10 @@ twa_status batch_groups(twa_batch *b) {
             most = std::max<long long>(most, g[i].want);
         }
         int per_cu = 0;
-        BHIP_TRY(b, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kGroupBatchBlock, b->group_lds));
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kGroupBatchBlock, b->group_lds) != hipSuccess) {
+            (void)hipGetLastError();
+            return TWA_OK;
+        }
         if (slots <= (long long)std::max(1, per_cu) * cus || most == 1) break;
     }
     std::stable_sort(order.begin(), order.end());
@@ -3655,8 +3684,8 @@ twa_status twa_batch_create(int n, const twa_instance *inst, unsigned flags, voi
     for (int i = 0; i < n; ++i) {
         const twa_instance &I = inst[i];
         twa_solver *s = nullptr;
-        twa_status st = twa_create(I.p, I.eta, I.dim, I.radii, I.x0, I.xT, I.n_walls, I.walls, I.C, I.rho0, I.alpha,
-                                   flags, b->stream, &s);
+        twa_status st = create_solver(I.p, I.eta, I.dim, I.radii, I.x0, I.xT, I.n_walls, I.walls, I.C, I.rho0,
+                                      I.alpha, flags, b->stream, true, &s);
         if (st == TWA_OK && I.z0) {
             st = twa_set_init(s, I.z0);
             if (st != TWA_OK) twa_destroy(s);
@@ -3718,11 +3747,6 @@ twa_status twa_batch_create(int n, const twa_instance *inst, unsigned flags, voi
         twa_batch_destroy(b);
         return TWA_E_DEVICE;
     }
-    const twa_status gst = batch_groups(b);
-    if (gst != TWA_OK) {
-        twa_batch_destroy(b);
-        return gst;
-    }
     *out = b;
     return TWA_OK;
 }
@@ -3731,6 +3755,8 @@ twa_status twa_batch_config(twa_batch *b, int block, int groups) {
     if (!b) return TWA_E_INVALID;
     if (b->latched != TWA_OK) return b->latched;
     if (block == 0) {
+        const twa_status st = batch_groups(b);
+        if (st != TWA_OK) return st;
         b->block = 0;
         drop_graph(b);
         return TWA_OK;
