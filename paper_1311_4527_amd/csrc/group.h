@@ -25,11 +25,12 @@
 // every member has read it, and written again from iteration t + 3 on; so
 // one barrier per iteration is enough.
 //
-// Only workgroups that already run are ever waited for.  They register; the
-// first one waits a bounded time for the rest and then freezes the group at
-// whoever came.  Later workgroups see the frozen mark and leave, the members
-// share out all the shares.  No assumption about residency or dispatch order
-// is needed for progress or for the result (fewer members are just slower).
+// Only workgroups that already run are ever waited for without a bound that a
+// working card meets.  They register; the first one waits for the rest (see
+// group_join) and then freezes the group at whoever came.  Later workgroups see
+// the frozen mark and leave, the members share out all the shares.  No
+// assumption about residency or dispatch order is needed for progress or for
+// the result (fewer members are just slower).
 //
 // What bounds an iteration: the chain of latencies of one wave (100-agent
 // swap, 461 queued factors, 32 members, 24 k cycles = 10.4 us against 19.5 us
@@ -123,15 +124,33 @@ __device__ __forceinline__ void group_give_up(GroupCtl *c) {
     __hip_atomic_store(&c->stuck, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Join the group: members get their rank in *rank and the member count in
-// *size; false for a workgroup that came too late, or where a wait ran out.
-__device__ __forceinline__ bool group_join(GroupCtl *c, int want, unsigned *rank, unsigned *size) {
+// Join the group for K iterations: members get their rank in *rank and the
+// member count in *size; false for a workgroup that came too late, or where a
+// wait ran out.
+//
+// A group that starts short stays short for all K iterations, however soon the
+// card is free again, so the first member waits for the rest for as long as
+// running without them would take longer: rounds of shares past the first, at
+// kGroupRound each, and 50 us at least.  What is lost by not starting, or by
+// starting and staying short, is then at most about the time that is needed
+// anyway.  (On an idle card all are there within a few us.  256 agents and 32
+// walls, 50 iterations, beside matrix products of 1 ms each on another stream:
+// with a fixed wait of 50 us some launches started short and took 26-34 ms,
+// now 1.9-2.7.)
+constexpr unsigned long long kGroupRound = 1000; // 10 us of the 100 MHz wall clock
+__device__ __forceinline__ bool group_join(GroupCtl *c, int want, int K, unsigned *rank, unsigned *size) {
     const unsigned stuck = agent_load(&c->stuck), r = atomicAdd(&c->reg, 1u);
     if (stuck || (r & kGroupFrozen)) return false;
     if (r == 0u) {
-        // about 50 us for the rest of the launch to arrive
-        for (int n = 0; n < 128 && agent_load(&c->reg) < (unsigned)want; ++n) __builtin_amdgcn_s_sleep(1);
-        const unsigned m = min(atomicOr(&c->reg, kGroupFrozen), (unsigned)want);
+        const unsigned long long t0 = wall_clock64();
+        unsigned m = 1u;
+        for (unsigned n = 0; n < kGroupPatience / 8; ++n) {
+            if ((m = agent_load(&c->reg)) >= (unsigned)want) break;
+            const unsigned long long more = ((unsigned)want + m - 1u) / m - 1u;
+            if (wall_clock64() - t0 > max(5 * kGroupRound, kGroupRound * K * more)) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        m = min(atomicOr(&c->reg, kGroupFrozen), (unsigned)want);
         __hip_atomic_store(&c->size, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *size = m;
     } else {
@@ -695,7 +714,7 @@ __global__ __launch_bounds__(kGroupBlock) void k_group(Params P, GroupArgs A) {
     __shared__ unsigned who[3];
     if (threadIdx.x == 0) {
         unsigned r = 0u, m = 0u;
-        who[2] = group_join(A.ctl, A.want, &r, &m) ? 1u : 0u;
+        who[2] = group_join(A.ctl, A.want, A.K, &r, &m) ? 1u : 0u;
         who[0] = r, who[1] = m;
     }
     __syncthreads();
@@ -753,7 +772,7 @@ __global__ __launch_bounds__(kGroupBatchBlock, 3) void kp_group(const Params *in
     in_global(A.words, base, at), in_global(A.sent, base, at);
     if (threadIdx.x == 0) {
         unsigned r = 0u, m = 0u;
-        who[2] = group_join(A.ctl, A.want, &r, &m) ? 1u : 0u;
+        who[2] = group_join(A.ctl, A.want, A.K, &r, &m) ? 1u : 0u;
         who[0] = r, who[1] = m;
     }
     __syncthreads();

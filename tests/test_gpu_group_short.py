@@ -1,0 +1,91 @@
+"""Groups with fewer members than shares: the members run all shares in turn, to
+the same bits; and a group waits for its members while that is shorter than
+running without them."""
+import ctypes as ct
+
+import pytest
+
+from paper_1311_4527_amd import instances as I
+from tests.test_gpu_batch_groups import MEMBERS
+from tests.test_gpu_group import CASES, F_ADMM, F_DENSE, F_VO, _plain, _same
+
+pytestmark = pytest.mark.gpu
+
+
+def _members(S, workgroups):
+    """(members of the last launch, shares); later launches start `workgroups`."""
+    from paper_1311_4527_amd import twa as T
+    size, shares = ct.c_int(), ct.c_int()
+    assert T.load_library().twa_debug_group_members(S.h, workgroups, ct.byref(size), ct.byref(shares)) == T.TWA_OK
+    return size.value, shares.value
+
+
+SCENES = {
+    "swap100": (CASES["swap100"], 0),                  # queues past a wave
+    "walls_3_units": (CASES["box9_walls"], 0),         # shares without any walls
+    "odd_3d": (CASES["swap26_odd_eta"], 0),
+    "64_shares": (CASES["box128_64_shares"], 0),
+    "dense": (CASES["box65_rows_of_64"], F_DENSE),
+    "admm": (CASES["box65_rows_of_64"], F_ADMM),       # queues emptied within an iteration
+    "vo": (lambda: I.circle_swap(60, 0.02, 1, seed=5, alpha=0.1, C=0.05), F_VO),
+}
+
+
+@pytest.mark.parametrize("scene", sorted(SCENES))
+@pytest.mark.parametrize("workgroups", [1, 5, -1])
+def test_short_group_equals_plain(scene, workgroups):
+    from paper_1311_4527_amd.twa import Solver
+    make, flags = SCENES[scene]
+    inst = make()
+    A, B = Solver.from_instance(inst, flags=flags), Solver.from_instance(inst, flags=flags)
+    shares = _members(A, 0)[1]
+    n = workgroups if workgroups > 0 else shares - 1
+    _members(A, n)
+    A.twa_iterate(8)             # a plain first iteration, then the short group
+    assert _members(A, 0)[0] == n
+    A.twa_iterate(6)             # a whole group takes the state over
+    assert _members(A, n)[0] == shares
+    A.twa_iterate(4)
+    _plain(B, 18)
+    _same(A, B)
+    A.close(), B.close()
+
+
+@pytest.mark.parametrize("members", ["large", "crowded"])
+@pytest.mark.parametrize("workgroups", [1, 3])
+def test_short_batch_groups_equal_plain(members, workgroups):
+    from paper_1311_4527_amd import twa as T
+    insts = MEMBERS[members]()
+    B = T.Batch(insts)
+    B.twa_batch_config(0, 1)
+    B.twa_batch_iterate(5)
+    assert T.load_library().twa_debug_batch_members(B.h, workgroups) == T.TWA_OK
+    B.twa_batch_iterate(9)
+    B.twa_batch_iterate(4)
+    for i, inst in enumerate(insts):
+        S = T.Solver.from_instance(inst)
+        _plain(S, 18)
+        _same(B.twa_batch_solver(i), S)
+        S.close()
+    B.close()
+
+
+def test_group_waits_for_its_members_on_a_busy_card():
+    """Beside another stream's work that frees compute units a few at a time,
+    every launch of 1000 iterations has all its members."""
+    import torch
+    from paper_1311_4527_amd.twa import Solver
+    S = Solver.from_instance(CASES["box200_128_shares"](), stream=torch.cuda.Stream())
+    S.twa_iterate(2)
+    a = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    out, other = torch.empty_like(a), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(6):
+        with torch.cuda.stream(other):
+            for _ in range(12):
+                torch.mm(a, a, out=out)
+        S.twa_iterate(1000)
+        size, shares = _members(S, 0)
+        torch.cuda.synchronize()
+        assert size == shares
+    S.close()
