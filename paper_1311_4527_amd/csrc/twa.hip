@@ -104,11 +104,7 @@ constexpr int kBlock = 256;
 // the appends of the whole grid do not serialise on one address.  A shard
 // holds every factor its waves could append (no overflow is possible).
 constexpr int kShards = 32;
-// Rows of the pair triangle that a wave of the activity-bit stream takes
-// together (coll_rows_bits); 1024 / 2048 agents and 32 walls: 2 rows 14.8 / 45.6
-// us, 4 rows 14.0 / 40.7, 6 rows 14.5 / 39.3.
-constexpr int kRows = 4;
-constexpr long long kWalkWaves = 8192; // see the walk in twa_create
+constexpr long long kWalkWaves = 8192; // see the walk in create_solver
 constexpr int kQueueStride = 64;
 
 enum Mode : int { M_FIRST = 0, M_FUSED = 1, M_FINAL = 2 };
@@ -497,6 +493,55 @@ __device__ __forceinline__ void row_masks(float4 mine, float radi, float rjj, co
     cpa_masks<D, NS>(ri, rj, R * R, act);
 }
 
+// The factors (i, j) of a wave's lanes in intervals s0 .. s0 + ns - 1, given
+// who is valid, the test's masks (completed here) and last iteration's activity
+// words (lanes from, from + 1, ... of mword): those to queue are appended, with
+// one atomic; in a capture, the rest is written.  c: the records of break-point
+// s0; jj: j, in bounds on idle lanes; me: the lane's bit.
+template <int D, int NS>
+__device__ __forceinline__ void queue_row(const Params &P, const float4 *c, int p, unsigned P2, int i, int j, int jj, int s0,
+                                          int ns, int lane, unsigned long long me, unsigned long long valid,
+                                          unsigned long long mword, int from, unsigned long long (&queue)[NS], unsigned *qs,
+                                          int *qlen) {
+    unsigned long long word[NS];
+    int n = 0;
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        word[k] = lane_value(mword, from + k);
+        queue[k] = k < ns ? (queue[k] & valid) | word[k] : 0ull;
+        n += __popcll(queue[k]);
+    }
+    // canonical index of (s, i, j): s p(p-1)/2 + fr (31 bits)
+    const unsigned fr = (unsigned)((long long)i * (2 * p - i - 1) / 2 + (j - i - 1));
+    if (capture_rest(P)) {
+        // capture of an iteration: the factors that stay inactive (x = n = z)
+        for (int k = 0; k < ns; ++k) {
+            unsigned long long qk = 0ull;
+#pragma unroll
+            for (int m = 0; m < NS; ++m) qk = m == k ? queue[m] : qk;
+            if (!(valid & ~qk & me)) continue;
+            const long long f = (s0 + k) * P2 + fr, e0 = P.e_coll + 4 * f;
+            if (P.dbg_x)
+                for (int e = 0; e < 4; ++e) {
+                    float zz[3];
+                    node_xyz(c[(k + (e & 1)) * p + (e < 2 ? i : jj)], zz, D);
+                    for (int q = 0; q < D; ++q) P.dbg_x[(e0 + e) * D + q] = zz[q];
+                }
+            P.dbg_rho[P.f_coll + f] = W_ZERO;
+        }
+    }
+    if (n == 0) return;
+    int base = 0;
+    if (lane == 0) base = atomicAdd(qlen, n);
+    base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        if (queue[k] & me)
+            qs[base + __popcll(queue[k] & (me - 1ull))] = ((s0 + k) * P2 + fr) | ((word[k] & me) ? kPrev : 0u);
+        base += __popcll(queue[k]);
+    }
+}
+
 // Collision factors (i, 64 J + lane) of up to ROWS rows i0 <= i < i1 in the
 // activity-bit form after the first iteration, ns <= NS intervals from s0.  A
 // factor that was inactive has u = 0, so its n is z and the test needs the
@@ -565,70 +610,51 @@ __device__ __forceinline__ void coll_rows_bits(const Params &P, const Rec &Z, in
         unsigned long long queue[NS];
         row_masks<D, NS>(mine, radi, rjj, rj, r, queue);
         const unsigned long long valid = tail & (i >= 64 * J ? ~0ull << (i - 64 * J + 1) : ~0ull);
-        unsigned long long word[NS];
-        int n = 0;
-#pragma unroll
-        for (int k = 0; k < NS; ++k) {
-            word[k] = lane_value(mword, r * NS + k);
-            queue[k] = k < ns ? (queue[k] & valid) | word[k] : 0ull;
-            n += __popcll(queue[k]);
-        }
-        // canonical index of (s, i, j): s p(p-1)/2 + fr (31 bits)
-        const unsigned fr = (unsigned)((long long)i * (2 * p - i - 1) / 2 + (j - i - 1));
-        if (capture_rest(P)) {
-            // capture of an iteration: the factors that stay inactive (x = n = z)
-            for (int k = 0; k < ns; ++k) {
-                unsigned long long qk = 0ull;
-#pragma unroll
-                for (int m = 0; m < NS; ++m) qk = m == k ? queue[m] : qk;
-                if (!(valid & ~qk & me)) continue;
-                const long long f = (s0 + k) * P2 + fr, e0 = P.e_coll + 4 * f;
-                if (P.dbg_x)
-                    for (int e = 0; e < 4; ++e) {
-                        float zz[3];
-                        node_xyz(c[(k + (e & 1)) * p + (e < 2 ? i : jj)], zz, D);
-                        for (int q = 0; q < D; ++q) P.dbg_x[(e0 + e) * D + q] = zz[q];
-                    }
-                P.dbg_rho[P.f_coll + f] = W_ZERO;
-            }
-        }
-        if (n == 0) continue;
-        int base = 0;
-        if (lane == 0) base = atomicAdd(qlen, n);
-        base = __builtin_amdgcn_readfirstlane(base);
-#pragma unroll
-        for (int k = 0; k < NS; ++k) {
-            if (queue[k] & me)
-                qs[base + __popcll(queue[k] & (me - 1ull))] = ((s0 + k) * P2 + fr) | ((word[k] & me) ? kPrev : 0u);
-            base += __popcll(queue[k]);
-        }
+        queue_row<D, NS>(P, c, p, P2, i, j, jj, s0, ns, lane, me, valid, mword, r * NS, queue, qs, qlen);
     }
 }
 
-// Collision column col: the pairs (i, j0 + lane), j0 a multiple of 64, of one
-// chunk of row i of the pair triangle (so i is the same for the whole wave;
-// lanes with j <= i are idle), over the break-point intervals s0 <= s < s1 <= s0 + CPW.
-// Every load of the column (node records of break-points s0..s1, agent i's
-// through the scalar cache when SCALAR_I, i.e. when Z points to global
-// memory; the chunks' activity words; u where it is read) is issued before
-// any factor is evaluated.  With clear_bits each chunk's activity word is
-// cleared after it was read (the minimisers set it again for the factors
-// active in this iteration).  Queued factors are appended to qs (length
-// *qlen).
+// As coll_rows_bits for one chunk (i, j0 + lane) of any j0 > i; leaves the
+// activity words for its caller to clear.
+template <int D, int NS>
+__device__ __forceinline__ void coll_chunk_bits(const Params &P, const Rec &Z, int i, int j0, int s0, int ns, int lane,
+                                                unsigned *qs, int *qlen) {
+    const int p = P.p, j = j0 + lane, jj = min(j, p - 1), cps = (int)P.cps, J = j0 >> 6, sh = j0 & 63;
+    const float4 *c = Z.cur + s0 * p;
+    // lane 2 k + h: word J + h of row i in interval s0 + k
+    const int wk = lane >> 1, wJ = J + (lane & 1);
+    const bool has = lane < 2 * NS && wk < ns && wJ <= (p - 1) >> 6;
+    const unsigned long long mword = has ? P.bits_coll[(s0 + wk) * cps + rowchunk(p, i) + wJ] : 0ull;
+    const float R = P.radii[i] + P.radii[jj];
+    float4 ri[NS + 1], rj[NS + 1];
+#pragma unroll
+    for (int k = 0; k <= NS; ++k) ri[k] = c[min(k, ns) * p + i], rj[k] = c[min(k, ns) * p + jj];
+    unsigned long long queue[NS];
+    cpa_masks<D, NS>(ri, rj, R * R, queue);
+    const unsigned long long valid = p - j0 < 64 ? (1ull << (p - j0)) - 1ull : ~0ull;
+    // interval k's bits of the chunk, on lane k
+    const unsigned long long lo = __shfl(mword, 2 * lane), hi = __shfl(mword, 2 * lane + 1);
+    const unsigned long long mine = sh ? (lo >> sh) | (hi << (64 - sh)) : lo;
+    queue_row<D, NS>(P, c, p, (unsigned)P.P2, i, j, jj, s0, ns, lane, 1ull << lane, valid, mine, 0, queue, qs, qlen);
+}
+
+// The pairs (i, j0 + lane) of row i of the pair triangle, i the same for the
+// whole wave (lanes with j <= i are idle), over the break-point intervals
+// s0 <= s < s1 <= s0 + CPW.  Every load (node records of break-points s0..s1,
+// agent i's through the scalar cache when SCALAR_I, i.e. when Z points to global
+// memory; the activity words; u where it is read) is issued before any factor
+// is evaluated.  (Activity-bit form: the first pass, of any j0 > i, and the
+// finalising one, where j0 is a multiple of 64 and cu the chunk's index in an
+// interval.)  With clear_bits each chunk's activity word is cleared after it was
+// read (the minimisers set it again for the factors active in this iteration).
+// Queued factors are appended to qs (length *qlen).
 template <int D, int MODE, int CPW, bool DENSE, bool SCALAR_I>
-__device__ __forceinline__ void coll_column(const Params &P, const Rec &Z, int col, int s0, int s1, int lane,
-                                            bool clear_bits, unsigned *qs, int *qlen) {
+__device__ __forceinline__ void coll_chunk(const Params &P, const Rec &Z, int i, int j0, int cu, int s0, int s1, int lane,
+                                           bool clear_bits, unsigned *qs, int *qlen) {
+    static_assert(DENSE || MODE != M_FUSED, "the activity-bit form tests whole masks there");
     constexpr bool need_prev = DENSE && MODE != M_FIRST;
     constexpr bool need_u = DENSE || MODE == M_FIRST;
     constexpr bool need_word = !DENSE && MODE != M_FIRST;
-    const int cu = __builtin_amdgcn_readfirstlane(col);
-    // (the dense stream has its own chunks: see the walk in twa_create)
-    const unsigned long long pk = load_uniform(DENSE && SCALAR_I ? P.walk_coll : P.chunk_coll, cu);
-    const int i = (int)((pk >> 24) & 0xffffffull), j0 = (int)(pk & 0xffffffull);
-    if constexpr (!DENSE && MODE == M_FUSED) {
-        coll_rows_bits<D, CPW, 1>(P, Z, i, i + 1, j0 >> 6, s0, s1 - s0, lane, clear_bits, qs, qlen);
-        return;
-    }
     const int p = P.p;
     const int j = j0 + lane;
     const bool valid = j > i && j < p;
@@ -689,6 +715,17 @@ __device__ __forceinline__ void coll_column(const Params &P, const Rec &Z, int c
 #pragma unroll
     for (int k = 0; k < CPW; ++k)
         if (s0 + k < s1) push(qs, qlen, q[k], val[k]);
+}
+
+// Column col of the walk: of the dense form's own chunks (see create_solver), or
+// of those that the activity words stand for.
+template <int D, int MODE, int CPW, bool DENSE, bool SCALAR_I>
+__device__ __forceinline__ void coll_column(const Params &P, const Rec &Z, int col, int s0, int s1, int lane,
+                                            bool clear_bits, unsigned *qs, int *qlen) {
+    const int cu = __builtin_amdgcn_readfirstlane(col);
+    const unsigned long long pk = load_uniform(DENSE ? P.walk_coll : P.chunk_coll, cu);
+    coll_chunk<D, MODE, CPW, DENSE, SCALAR_I>(P, Z, (int)((pk >> 24) & 0xffffffull), (int)(pk & 0xffffffull), cu, s0, s1,
+                                              lane, clear_bits, qs, qlen);
 }
 
 // Collision factors f0 + k step (k < U) of a flat walk over the canonical
@@ -1475,6 +1512,19 @@ __device__ __forceinline__ const Params &params_lds(const Params *src, Params *d
 // lengths are workgroup-local counters.
 constexpr int kBatchLdsNodes = 4000; // 62.5 KiB of node records per workgroup
 
+// Whether an instance of 64 agents or more is walked by kRows rows of a chunk
+// column per wave, which share their loads, rather than by the chunks of its
+// rows, which are fewer: beside the diagonal and at the last column, rows cut at
+// multiples of 64 leave most lanes idle.  us per iteration of 256 instances, eta =
+// 6, 256 / 512 lanes, by chunks and by rows: 66 agents 52 / 35, 67 / 44; 80: 68 /
+// 46, 76 / 51; 96: 89 / 57, 85 / 55; 128: 125 / 79, 99 / 63.  A task takes four
+// intervals: with three, 100 agents 38 and 41, 128 agents 49 and 47.  In 3-D, where
+// the test is longer, rows win earlier: 66 agents 34 and 43, 80: 47 and 44.  64
+// agents have no last column: 50 and 44.
+__device__ __forceinline__ bool batch_by_rows(const Params &P) {
+    return P.p == 64 || P.p >= (P.dim == 3 ? 72 : P.eta < 4 ? 112 : 96);
+}
+
 template <int D, int MODE, int BLOCK>
 __device__ __forceinline__ void batch_instance(const Params &P, float4 *zs, int *len) {
     const bool clear_bits = P.dense == 0;
@@ -1491,20 +1541,41 @@ __device__ __forceinline__ void batch_instance(const Params &P, float4 *zs, int 
         // rows of at least 64 pairs for the most part: the column walk of
         // the plain factor stream, wave by wave over (column, intervals)
         const unsigned w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const unsigned cps = (unsigned)P.cps;
         if (P.dense) {
-            const unsigned nw = cps * (unsigned)((P.eta + 1) / 2);
+            const unsigned per = (unsigned)P.nwalk, nw = per * (unsigned)((P.eta + 1) / 2);
             for (unsigned w = w0; w < nw; w += BLOCK / 64) {
-                const int s0 = (int)(w / cps) * 2;
-                coll_column<D, MODE, 2, true, false>(P, Z, (int)(w % cps), s0, min(s0 + 2, P.eta), threadIdx.x & 63,
+                const int s0 = (int)(w / per) * 2;
+                coll_column<D, MODE, 2, true, false>(P, Z, (int)(w % per), s0, min(s0 + 2, P.eta), threadIdx.x & 63,
                                                      false, P.qc, &len[0]);
             }
+        } else if (MODE == M_FIRST || !batch_by_rows(P)) {
+            const int per = pair_chunks(P.p);
+            for (int s0 = 0, w = (int)w0;; w += BLOCK / 64) {
+                for (; w >= per && s0 < P.eta; s0 += 4) w -= per;
+                if (s0 >= P.eta) break;
+                int i, j0;
+                pair_chunk(P.p, w, &i, &j0);
+                // (opaque: the compiler took i apart into a constant and the
+                // rest, and put the constant into the offset of the loads of
+                // agent i's records.  Those are flat ones, which find the LDS by
+                // their base alone, and the base lay in front of it.)
+                i = __builtin_amdgcn_readfirstlane(i), j0 = __builtin_amdgcn_readfirstlane(j0);
+                asm volatile("" : "+s"(i), "+s"(j0));
+                if constexpr (MODE == M_FIRST)
+                    coll_chunk<D, MODE, 4, false, false>(P, Z, i, j0, 0, s0, min(s0 + 4, P.eta), threadIdx.x & 63, false,
+                                                         P.qc, &len[0]);
+                else
+                    coll_chunk_bits<D, 4>(P, Z, i, j0, s0, min(4, P.eta - s0), threadIdx.x & 63, P.qc, &len[0]);
+            }
         } else {
-            const unsigned nw = cps * (unsigned)((P.eta + 3) / 4);
-            for (unsigned w = w0; w < nw; w += BLOCK / 64) {
-                const int s0 = (int)(w / cps) * 4;
-                coll_column<D, MODE, 4, false, false>(P, Z, (int)(w % cps), s0, min(s0 + 4, P.eta), threadIdx.x & 63,
-                                                      false, P.qc, &len[0]);
+            const int per = bits_walk(P.p);
+            for (int s0 = 0, w = (int)w0;; w += BLOCK / 64) {
+                for (; w >= per && s0 < P.eta; s0 += 4) w -= per;
+                if (s0 >= P.eta) break;
+                int i0, J;
+                bits_task(P.p, w, &i0, &J);
+                coll_rows_bits<D, 4, kRows>(P, Z, i0, min(i0 + kRows, P.p - 1), J, s0, min(4, P.eta - s0),
+                                            threadIdx.x & 63, false, P.qc, &len[0]);
             }
         }
     } else {
@@ -1516,8 +1587,10 @@ __device__ __forceinline__ void batch_instance(const Params &P, float4 *zs, int 
     // still takes consecutive factors): in a small instance the kinds run
     // side by side instead of one after another on the first waves.
     auto round64 = [](long long n) { return (int)((std::min<long long>(n, BLOCK) + 63) / 64 * 64); };
-    const long long lanes_c =
-        P.p >= 64 ? 64LL * P.cps * (P.dense ? (P.eta + 1) / 2 : (P.eta + 3) / 4) : P.Fc;
+    const long long lanes_c = P.p < 64  ? P.Fc
+                              : P.dense ? 64LL * P.nwalk * ((P.eta + 1) / 2)
+                                        : 64LL * (MODE == M_FIRST || !batch_by_rows(P) ? pair_chunks(P.p) : bits_walk(P.p)) *
+                                              ((P.eta + 3) / 4);
     const int shift_w = round64(lanes_c) % BLOCK;
     const int shift_e = (shift_w + round64(P.Fw)) % BLOCK;
     const int shift_f = (shift_e + round64(P.Fe)) % BLOCK;
