@@ -2438,24 +2438,38 @@ bool group_attr() {
 
 // Mid-sized instances (beyond the one-workgroup path, up to this many
 // collision + wall factors, node records within a workgroup's LDS) run their
-// steady iterations in a group of resident workgroups.  us per iteration,
-// three launches against the group: 3k factors 18.5 / 8.6, 16k 19.3 / 9.0, 40k
-// 19.5 / 10.4, 261k 20.1 / 14.7, 653k (walls) 23.3 / 20.8; ADMM at 3k 21.1 /
-// 10.4.  Past that the walk of 128 members takes as long as the launches save.
-constexpr long long kGroupFactors = 700000;
+// steady iterations in a group of resident workgroups, of 32 shares, or 64 or
+// 128 from so many factors per share on.  Both lines depend on the form.  Activity
+// bits: a member's walk takes about 1 us per 2,000 factors, a barrier of 32 / 64 /
+// 128 members 0.9 / 1.4 / 2.1 us.  The dense form reads u of every factor too, and
+// ADMM runs every factor's minimiser, for which three launches have the whole card.
+// us per iteration, three launches against the group, by shares 32, 64, 128:
+//   bits   156k 15.8 / 13.7, 11.7, 11.4;  318k 16.9 / 18.5, 14.8, 13.3;  522k 17.0 /
+//          21.0, 16.1, 14.2;  704k 18.1 / 25.5, 18.5, 16.1;  with walls 653k 21.8 /
+//          34.7, 24.0, 19.7;  819k 21.8 / 42, 28, 22.8
+//   dense  32k 16.9 / 11.8, 10.9, 11.4;  79k 16.7 / 17.8, 14.1, 13.4;  204k 16.8 / 28.9,
+//          19.6, 16.0;  261k 16.6 / 29, 21, 16.9;  318k 17.7 / 39, 26, 19.9
+//   ADMM   6k 22.6 / 12.3, 12.8, 18.2;  16k 24.1 / 18.4, 12.3, 14.6;  32k 28.2 / 27.9,
+//          19.1, 18.9;  65k 35.1 / 43, 31, 25.3;  79k 34.8 / 70, 46, 36.4;  156k 43.6 /
+//          130, 88, 62
+struct GroupRule {
+    long long most, per_share;
+};
+GroupRule group_rule(const Params &P) {
+    if (P.admm) return {70000, 300};
+    if (P.dense) return {230000, 1000};
+    return {700000, 2250};
+}
 
 // Choose the group of a mid-sized instance and allocate what its launches
 // share; leaves s->group_want 0 where the plain launches are kept, also where
 // there is no memory for the group (they need none).
 twa_status prepare_group(twa_solver *s) {
     const Params &P = s->P;
-    if (P.Fc + P.Fw > kGroupFactors) return TWA_OK;
-    // Shares: a member's walk takes about 1 us per 2,000 factors, a barrier
-    // of 32 / 64 / 128 members 0.9 / 1.4 / 2.1 us.  us per iteration with 32,
-    // 64, 128 shares: 40k factors 10.4, 10.6, 11.7; 110k (walls) 16.4, 14.0,
-    // 14.3; 261k 18.7, 15.5, 14.7; 653k (walls) 36, 25, 20.8.
+    const GroupRule rule = group_rule(P);
+    if (P.Fc + P.Fw > rule.most) return TWA_OK;
     int want = 32;
-    while (want < 128 && P.Fc + P.Fw >= 2250LL * want) want *= 2;
+    while (want < 128 && P.Fc + P.Fw >= rule.per_share * want) want *= 2;
     GroupLds L;
     unsigned bytes;
     if (!group_layout(s, want, kGroupBlock, &L, &bytes)) return TWA_OK;
