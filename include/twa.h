@@ -383,11 +383,12 @@ twa_status twa_batch_create(int n, const twa_instance *inst, unsigned flags, voi
  * many lanes per workgroup and `groups` workgroups (bins; clamped to n);
  * instances are packed onto bins longest-first and each bin runs all k
  * iterations of its instances in one launch.  block 0 (groups ignored):
- * a large instance spreads over many compute units.  Without TWA_F_DENSE
- * every instance has a group of resident workgroups sized by its factors
- * and all k iterations run in one launch; with it, and where an instance
- * does not fit, one launch per phase of an iteration (factor stream,
- * minimisers, consensus) covers the blocks of every instance.  Either way the evolution is bitwise that of the
+ * a large instance spreads over many compute units.  Every instance has a
+ * group of resident workgroups sized by its factors and all k iterations run
+ * in one launch; with TWA_F_DENSE or TWA_F_ADMM, and where an instance does
+ * not fit or is too large for its group to be the faster way, one launch per
+ * phase of an iteration (factor stream, minimisers, consensus) covers the
+ * blocks of every instance.  Either way the evolution is bitwise that of the
  * instances' own solvers.  Default: 256 lanes, one bin per instance. */
 twa_status twa_batch_config(twa_batch *b, int block, int groups);
 

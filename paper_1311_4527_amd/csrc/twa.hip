@@ -3458,13 +3458,14 @@ twa_status twa_debug_group_stuck(twa_solver *s, int batch) {
 
 // For the tests of groups that start short (not declared in the header): later
 // launches of this solver's group start `workgroups` of its workgroups only
-// (0: all).  *size, *shares: members of the last launch, and of a whole group.
+// (0: all).  *size, *shares: members of the last launch (of a batch's instance:
+// of its group there), and of a whole group of its own.
 twa_status twa_debug_group_members(twa_solver *s, int workgroups, int *size, int *shares) {
     TRY(check_alive(s));
-    if (!s->group_ctl || workgroups < 0 || !size || !shares) return fail(s, TWA_E_STATE, "no group");
+    const GroupCtl *ctl = static_cast<const GroupCtl *>(s->group_ctl ? s->group_ctl : s->batch_ctl);
+    if (!ctl || workgroups < 0 || !size || !shares) return fail(s, TWA_E_STATE, "no group");
     unsigned m = 0;
-    HIP_TRY(s, hipMemcpyAsync(&m, &static_cast<const GroupCtl *>(s->group_ctl)->size, sizeof(m), hipMemcpyDeviceToHost,
-                              s->stream));
+    HIP_TRY(s, hipMemcpyAsync(&m, &ctl->size, sizeof(m), hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(s, hipStreamSynchronize(s->stream));
     *size = (int)m, *shares = s->group_want;
     s->group_launch = workgroups;
@@ -3587,16 +3588,27 @@ twa_status batch_bins(twa_batch *b) {
 
 // The groups of a batch: shares by work, as many as the device holds at once
 // (workgroups past that would run after the first ones' last iteration; the
-// target grows until they fit, or every instance has one), and the blocks'
-// instances in an order that keeps a group on one XCD (blocks go to the 8 XCDs
-// in turn) and starts the large groups first.  A share has 1500 factors at
-// least, about six per lane: less and the barrier is most of the iteration.
+// target grows until they fit), and the blocks' instances in an order that keeps
+// a group on one XCD (blocks go to the 8 XCDs in turn) and starts the large
+// groups first.  More instances than fit at once take turns in any case: then
+// only the groups of several shares, which start first, have to fit (1000
+// instances of 16 agents and one of 200, 16 intervals: one share each 336 us per
+// iteration, shares by work 38, phased 45).  A share has 1500 factors at least,
+// about six per lane: less and the barrier is most of the iteration.
 // Made when block 0 is first asked for.  Leaves n_slots 0, and the phased
 // launches in use, where an instance does not fit a workgroup's LDS, where
-// there is no memory for the groups, and in the
-// dense form: it streams u of every factor, which the phased kernel has more
-// waves in flight for (64 instances 57 us per iteration, in groups 65; 16
-// instances 26 against 42).
+// there is no memory for the groups, and where the phased launches are faster
+// (us per iteration, phased / groups):
+//   in the dense form: it streams u of every factor, which the phased kernel has
+//   more waves in flight for (64 instances 57 / 65; 16 instances 26 / 42);
+//   for an instance past 750,000 factors, or past 300,000 among fewer than four:
+//   its 64 shares are too few (1.05 M factors: 1 instance 20 / 44, 4 28 / 46, 16 61
+//   / 64; 704k: 8 33 / 27, 64 160 / 161; 522k: 1 19 / 23, 2 20 / 22, 4 23 / 22; 261k: 1
+//   18 / 16);
+//   where an instance leaves a compute unit no LDS for a second workgroup, with
+//   fewer than eight instances or past 250,000 factors on average: four waves per
+//   unit (4300 nodes of 292k factors: 1 15 / 23, 4 21 / 23, 8 26 / 24, 64 94 / 104; 522k:
+//   64 130 / 160; one such among 300 small ones 44 / 39).
 twa_status batch_groups(twa_batch *b) {
     if (b->n_slots > 0) return TWA_OK;
     const int n = (int)b->solvers.size();
@@ -3609,14 +3621,19 @@ twa_status batch_groups(twa_batch *b) {
         (void)hipGetLastError();
         return TWA_OK;
     }
-    long long total = 0;
-    for (twa_solver *s : b->solvers) total += s->P.Fc + s->P.Fw;
+    long long total = 0, largest = 0;
+    for (twa_solver *s : b->solvers) {
+        total += s->P.Fc + s->P.Fw;
+        largest = std::max(largest, s->P.Fc + s->P.Fw);
+    }
+    if (largest > (n < 4 ? 300000 : 750000)) return TWA_OK;
     std::vector<GroupArgs> g((size_t)n);
     std::vector<std::pair<int, int>> order; // (-shares, instance)
+    std::vector<std::vector<int>> column(8);
     for (double target = std::max(1500.0, (double)total / (3.0 * cus));; target *= 1.1) {
         order.clear();
         b->group_lds = 0;
-        long long slots = 0, most = 0;
+        int most = 0;
         for (int i = 0; i < n; ++i) {
             twa_solver *s = b->solvers[i];
             unsigned bytes;
@@ -3626,22 +3643,26 @@ twa_status batch_groups(twa_batch *b) {
             if (!group_layout(s, g[i].want, kGroupBatchBlock, &g[i].L, &bytes)) return TWA_OK;
             b->group_lds = std::max(b->group_lds, bytes);
             order.emplace_back(-g[i].want, i);
-            slots += g[i].want;
-            most = std::max<long long>(most, g[i].want);
+            most = std::max(most, g[i].want);
         }
         int per_cu = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kGroupBatchBlock, b->group_lds) != hipSuccess) {
             (void)hipGetLastError();
             return TWA_OK;
         }
-        if (slots <= (long long)std::max(1, per_cu) * cus || most == 1) break;
-    }
-    std::stable_sort(order.begin(), order.end());
-    std::vector<std::vector<int>> column(8);
-    for (const auto &o : order) {
-        auto &c = *std::min_element(column.begin(), column.end(),
-                                    [](const std::vector<int> &x, const std::vector<int> &y) { return x.size() < y.size(); });
-        c.insert(c.end(), (size_t)-o.first, o.second);
+        if (per_cu < 2 && (n < 8 || total > 250000LL * n)) return TWA_OK;
+        const size_t room = (size_t)std::max(1, per_cu) * cus / 8; // workgroups that an XCD holds at once
+        std::stable_sort(order.begin(), order.end());
+        size_t shared = 0, longest = 0; // of the columns: with several shares, and in all
+        for (auto &c : column) c.clear();
+        for (const auto &o : order) {
+            auto &c = *std::min_element(column.begin(), column.end(),
+                                        [](const std::vector<int> &x, const std::vector<int> &y) { return x.size() < y.size(); });
+            c.insert(c.end(), (size_t)-o.first, o.second);
+            longest = std::max(longest, c.size());
+            if (o.first < -1) shared = longest;
+        }
+        if (longest <= room || most == 1 || ((size_t)n > 8 * room && shared <= room)) break;
     }
     std::vector<int> slots;
     for (size_t r = 0;; ++r) {

@@ -7,7 +7,7 @@ import pytest
 
 from paper_1311_4527_amd import instances as I
 from tests.test_gpu_batch_groups import MEMBERS
-from tests.test_gpu_group import CASES, F_ADMM, F_DENSE, F_VO, _plain, _same
+from tests.test_gpu_group import CASES, F_ADMM, F_DENSE, F_VO, _box, _plain, _same
 
 pytestmark = pytest.mark.gpu
 
@@ -51,11 +51,17 @@ def test_short_group_equals_plain(scene, workgroups):
     A.close(), B.close()
 
 
-@pytest.mark.parametrize("members", ["large", "crowded"])
+BATCHES = {
+    "large": lambda: [_box(200, 16, 7), _box(20, 4, 4), _box(66, 5, 0, dim=3), _box(1, 3, 2)],  # 64 shares beside one
+    "crowded": MEMBERS["crowded"],
+}
+
+
+@pytest.mark.parametrize("members", sorted(BATCHES))
 @pytest.mark.parametrize("workgroups", [1, 3])
 def test_short_batch_groups_equal_plain(members, workgroups):
     from paper_1311_4527_amd import twa as T
-    insts = MEMBERS[members]()
+    insts = BATCHES[members]()
     B = T.Batch(insts)
     B.twa_batch_config(0, 1)
     B.twa_batch_iterate(5)
