@@ -201,9 +201,9 @@ twa_status twa_set_schedule(twa_solver *s, float rho0_init, int n_warm);
  * (captured together the first time, so any k replays); an instance of at
  * most 256 collision + wall factors (or 512 collision factors and no walls)
  * runs them in one persistent single-workgroup launch instead, and a
- * mid-sized one (up to 700,000 factors, dense 230,000, ADMM 70,000, whose
- * break-points fit a workgroup's LDS) in one launch of a group of resident
- * workgroups (bitwise the same iterations). */
+ * mid-sized one (up to 700,000 factors, dense 230,000, ADMM 70,000, and at
+ * most 5,000 break-points, fewer where few agents have them) in one launch of
+ * a group of resident workgroups (bitwise the same iterations). */
 twa_status twa_iterate(twa_solver *s, int k);
 
 /* Iterate until the plan is collision-free: up to max_iter >= 0 iterations

@@ -2452,13 +2452,21 @@ bool group_attr() {
 //   ADMM   6k 22.6 / 12.3, 12.8, 18.2;  16k 24.1 / 18.4, 12.3, 14.6;  32k 28.2 / 27.9,
 //          19.1, 18.9;  65k 35.1 / 43, 31, 25.3;  79k 34.8 / 70, 46, 36.4;  156k 43.6 /
 //          130, 88, 62
+// Every member updates all nodes, about 1.2 us per 1000 (dense: 2, with last
+// iteration's records), which three launches share out.  Long paths of few agents,
+// whose walk and minimisers are short, keep those: 20 agents of 400 intervals 12.0
+// / 16.1, of 200 11.4 / 11.7;  3 of 1500 9.1 / 11.0;  8 of 250 10.3 / 7.8;  64 of 120
+// 12.5 / 16.1, of 60 17.2 / 11.2;  dense 10 of 400 10.6 / 18.9, 8 of 250 10.7 / 11.5, of
+// 100 11.4 / 8.2, 64 of 60 16.9 / 14.8;  ADMM 5 of 800 17.8 / 20.6, 8 of 250 18.0 / 14.9.
 struct GroupRule {
     long long most, per_share;
+    int crowd;            // agents from which
+    long long nodes, few; // so many nodes are allowed; and below that
 };
 GroupRule group_rule(const Params &P) {
-    if (P.admm) return {70000, 300};
-    if (P.dense) return {230000, 1000};
-    return {700000, 2250};
+    if (P.admm) return {70000, 300, 20, 5000, 3000};
+    if (P.dense) return {230000, 1000, 64, 5000, 1800};
+    return {700000, 2250, 40, 5000, 3700};
 }
 
 // Choose the group of a mid-sized instance and allocate what its launches
@@ -2467,7 +2475,7 @@ GroupRule group_rule(const Params &P) {
 twa_status prepare_group(twa_solver *s) {
     const Params &P = s->P;
     const GroupRule rule = group_rule(P);
-    if (P.Fc + P.Fw > rule.most) return TWA_OK;
+    if (P.Fc + P.Fw > rule.most || P.N > (P.p < rule.crowd ? rule.few : rule.nodes)) return TWA_OK;
     int want = 32;
     while (want < 128 && P.Fc + P.Fw >= rule.per_share * want) want *= 2;
     GroupLds L;

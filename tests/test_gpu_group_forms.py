@@ -22,6 +22,9 @@ def _shares(S):
     (F_DENSE, 60, 8, 0, 32), (F_DENSE, 90, 10, 0, 64), (F_DENSE, 160, 16, 0, 128), (F_DENSE, 200, 16, 0, 0),
     (F_ADMM, 40, 8, 0, 32), (F_ADMM, 60, 8, 5, 64), (F_ADMM, 100, 8, 0, 128), (F_ADMM, 40, 8, 60, 128),
     (F_ADMM, 100, 16, 0, 0),
+    # many nodes of few agents
+    (0, 20, 150, 0, 32), (0, 20, 200, 0, 0), (0, 64, 70, 0, 64), (0, 64, 80, 0, 0), (F_DENSE, 8, 200, 0, 32),
+    (F_DENSE, 8, 250, 0, 0), (F_ADMM, 5, 500, 0, 32), (F_ADMM, 5, 700, 0, 0),
 ])
 def test_shares_by_form(flags, p, eta, walls, shares):
     from paper_1311_4527_amd.twa import Solver
