@@ -183,6 +183,7 @@ struct twa_solver {
     float *group_xe = nullptr;
     unsigned char *group_sent = nullptr;
     int group_want = 0;
+    int group_least = 1; // calls of fewer iterations keep the plain launches
     int group_launch = 0; // (tests) workgroups its launches start, 0: all
     void *batch_ctl = nullptr; // shared words of this instance's group in its batch
     // TWA_F_TAPE: the state the differentiated run starts from (canonical

@@ -2508,6 +2508,12 @@ twa_status prepare_group(twa_solver *s) {
     s->group_xe = reinterpret_cast<float *>(m + o_xe);
     s->group_sent = reinterpret_cast<unsigned char *>(m + o_sent);
     s->group_want = want;
+    // A launch costs 6-13 us beside its iterations (records into LDS, the group's
+    // start), by members.  us a call, plain / group: 200 agents, 16 intervals (128
+    // shares) of one iteration 22 / 26, two 44 / 43; 80 of 40 intervals (64) one 20 /
+    // 23, two 42 / 39; dense 140 of 16 (128) two 43 / 49, four 82 / 84, eight 162 / 156;
+    // 100 agents (32) one 23 / 20.
+    s->group_least = want == 32 ? 1 : want == 128 && P.dense && !P.admm ? 6 : 2;
     return TWA_OK;
 }
 
@@ -2577,7 +2583,7 @@ twa_status iterate_core(twa_solver *s, int k, bool timed) {
     while (k > 0) {
         const bool steady = s->pending && s->iter - 1 >= s->n_warm && !s->dbg_rho && !s->adj_pool;
         // (a timed call times the plain kernels, so it runs them throughout)
-        if (steady && !timed && s->group_want > 0) {
+        if (steady && !timed && s->group_want > 0 && k >= s->group_least) {
             TRY(iterate_group(s, k));
             k = 0;
             continue;
@@ -3973,7 +3979,9 @@ twa_status twa_batch_iterate(twa_batch *b, int k) {
             launch_batch(b, 1, 1);
             --left;
         }
-        if (left > 0 && b->n_slots > 0) {
+        // (one iteration is faster phased: 4 instances of 100 agents 24 us and 31,
+        // 1000 of 20 46 and 55; two are not: 52 and 46, 95 and 78)
+        if (left > 1 && b->n_slots > 0) {
             launch_groups(b, left);
             left = 0;
         }
