@@ -1525,7 +1525,10 @@ __device__ __forceinline__ bool batch_by_rows(const Params &P) {
     return P.p == 64 || P.p >= (P.dim == 3 ? 72 : P.eta < 4 ? 112 : 96);
 }
 
-template <int D, int MODE, int BLOCK>
+// WIDE: the instance may have 64 agents or more.  (Without those walks the kernel
+// of small instances spills less; 1000 of 20 agents, us per iteration with 256 /
+// 1024 lanes: 32.6 / 71 with them, 31.3 / 59 without.)
+template <int D, int MODE, int BLOCK, bool WIDE>
 __device__ __forceinline__ void batch_instance(const Params &P, float4 *zs, int *len) {
     const bool clear_bits = P.dense == 0;
     const bool stage = P.N <= kBatchLdsNodes;
@@ -1537,7 +1540,7 @@ __device__ __forceinline__ void batch_instance(const Params &P, float4 *zs, int 
     if (threadIdx.x == 0) len[0] = len[1] = 0;
     __syncthreads();
     const Rec Z{stage ? zs : P.zr_cur, stage_prev ? zs + P.N : P.zr_prev};
-    if (P.p >= 64) {
+    if (WIDE && P.p >= 64) {
         // rows of at least 64 pairs for the most part: the column walk of
         // the plain factor stream, wave by wave over (column, intervals)
         const unsigned w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1587,7 +1590,7 @@ __device__ __forceinline__ void batch_instance(const Params &P, float4 *zs, int 
     // still takes consecutive factors): in a small instance the kinds run
     // side by side instead of one after another on the first waves.
     auto round64 = [](long long n) { return (int)((std::min<long long>(n, BLOCK) + 63) / 64 * 64); };
-    const long long lanes_c = P.p < 64  ? P.Fc
+    const long long lanes_c = !WIDE || P.p < 64 ? P.Fc
                               : P.dense ? 64LL * P.nwalk * ((P.eta + 1) / 2)
                                         : 64LL * (MODE == M_FIRST || !batch_by_rows(P) ? pair_chunks(P.p) : bits_walk(P.p)) *
                                               ((P.eta + 3) / 4);
@@ -1629,7 +1632,7 @@ __device__ __forceinline__ void batch_instance(const Params &P, float4 *zs, int 
     __syncthreads();
 }
 
-template <int BLOCK>
+template <int BLOCK, bool WIDE>
 __global__ __launch_bounds__(BLOCK) void k_batch(const Params *insts, const int *bin_start, const int *bin_items,
                                                   int K, int first) {
     __shared__ float4 zs[kBatchLdsNodes];
@@ -1642,11 +1645,11 @@ __global__ __launch_bounds__(BLOCK) void k_batch(const Params *insts, const int 
         for (int q = q0; q < q1; ++q) {
             const Params &P = params_lds<BLOCK>(insts + bin_items[q], &sp);
             if (P.dim == 2) {
-                if (fst) batch_instance<2, M_FIRST, BLOCK>(P, zs, len);
-                else batch_instance<2, M_FUSED, BLOCK>(P, zs, len);
+                if (fst) batch_instance<2, M_FIRST, BLOCK, WIDE>(P, zs, len);
+                else batch_instance<2, M_FUSED, BLOCK, WIDE>(P, zs, len);
             } else {
-                if (fst) batch_instance<3, M_FIRST, BLOCK>(P, zs, len);
-                else batch_instance<3, M_FUSED, BLOCK>(P, zs, len);
+                if (fst) batch_instance<3, M_FIRST, BLOCK, WIDE>(P, zs, len);
+                else batch_instance<3, M_FUSED, BLOCK, WIDE>(P, zs, len);
             }
         }
     }
@@ -2390,7 +2393,7 @@ twa_status iterate_tiny(twa_solver *s, int k) {
             hipLaunchKernelGGL(k_tiny<kTinyBlock>, dim3(1), dim3(kTinyBlock), L.total, s->stream,
                                (const Params *)s->tiny_params, L, n, s->pending ? 0 : 1, 0, 0.0, (int *)nullptr);
         else
-            hipLaunchKernelGGL(k_batch<kTinyBlock>, dim3(1), dim3(kTinyBlock), 0, s->stream,
+            hipLaunchKernelGGL((k_batch<kTinyBlock, false>), dim3(1), dim3(kTinyBlock), 0, s->stream,
                                (const Params *)s->tiny_params, (const int *)s->tiny_bins,
                                (const int *)s->tiny_bins + 2, n, s->pending ? 0 : 1);
         HIP_TRY(s, hipGetLastError());
@@ -3521,6 +3524,7 @@ struct twa_batch {
     Params *insts_dev = nullptr;
     int *bin_start_dev = nullptr, *bin_items_dev = nullptr;
     int block = 256, groups = 0;       // block 0: the phased form
+    bool wide = false;                 // some instance has 64 agents or more
     int2 *map_dev = nullptr;           // phased form: stream, queue, node block maps
     int n_stream = 0, n_queue = 0, n_nodes = 0;
     hipGraphExec_t pexec = nullptr;    // phased form: kPhasedChunk iterations
@@ -3766,16 +3770,14 @@ void launch_batch(twa_batch *b, int k, int first) {
         }
         return;
     }
-    dim3 grid(b->groups);
-    if (b->block == 1024)
-        hipLaunchKernelGGL(k_batch<1024>, grid, dim3(1024), 0, b->stream, (const Params *)b->insts_dev,
+    const dim3 grid(b->groups), block(b->block);
+    const auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, b->stream, (const Params *)b->insts_dev,
                            (const int *)b->bin_start_dev, (const int *)b->bin_items_dev, k, first);
-    else if (b->block == 512)
-        hipLaunchKernelGGL(k_batch<512>, grid, dim3(512), 0, b->stream, (const Params *)b->insts_dev,
-                           (const int *)b->bin_start_dev, (const int *)b->bin_items_dev, k, first);
-    else
-        hipLaunchKernelGGL(k_batch<256>, grid, dim3(256), 0, b->stream, (const Params *)b->insts_dev,
-                           (const int *)b->bin_start_dev, (const int *)b->bin_items_dev, k, first);
+    };
+    if (b->block == 1024) b->wide ? run(k_batch<1024, true>) : run(k_batch<1024, false>);
+    else if (b->block == 512) b->wide ? run(k_batch<512, true>) : run(k_batch<512, false>);
+    else b->wide ? run(k_batch<256, true>) : run(k_batch<256, false>);
 }
 
 } // namespace
@@ -3836,6 +3838,7 @@ twa_status twa_batch_create(int n, const twa_instance *inst, unsigned flags, voi
             return st;
         }
         b->solvers.push_back(s);
+        b->wide = b->wide || s->p >= 64;
     }
     b->insts_dev = static_cast<Params *>(b->mem.get(sizeof(Params) * n, b->stream));
     b->bin_start_dev = static_cast<int *>(b->mem.get(sizeof(int) * (n + 1), b->stream));
