@@ -72,10 +72,14 @@ struct Adj {
     float *dx0, *dxT;    // [p][2], accumulated
     // Radius cotangents of agent i's factors of interval s, at node (i, s): with
     // one word per agent a crowded step waited for its atomics (15.2 -> 13.4 us).
-    double *drd;         // [N], accumulated
+    // One word per agent where the scratch has no room for more.
+    double *drd;         // [N], or [p] with drd_agents; accumulated
+    int drd_agents;
 };
 
 __device__ __forceinline__ long long node_id(const Adj &A, int i, int s) { return (long long)i * (A.eta + 1) + s; }
+// the word of drd for agent i's factors of the interval that starts at node t
+__device__ __forceinline__ double *drd_word(const Adj &A, int i, long long t) { return A.drd + (A.drd_agents ? i : t); }
 
 __device__ __forceinline__ long long pair_index(int p, int a, int b) {
     return (long long)a * p - (long long)a * (a + 1) / 2 + (b - a - 1);
@@ -304,8 +308,8 @@ __device__ __forceinline__ void adj_active(const Adj &A, const AdjRec &rec, Node
         for (int qq = 0; qq < 8; ++qq) nbv[qq] = 0.f;
         float Rb = 0.f;
         coll_vjp2(rec.n, w, k, R, xb, nbv, Rb);
-        atomicAdd(&A.drd[t[0]], (double)Rb);
-        atomicAdd(&A.drd[t[2]], (double)Rb);
+        atomicAdd(drd_word(A, i, t[0]), (double)Rb);
+        atomicAdd(drd_word(A, j, t[2]), (double)Rb);
         out.ne = 4;
         for (int qq = 0; qq < 4; ++qq)
             out.t[qq] = t[qq], out.v[qq] = edge_out(A, e0 + qq, up[qq], mk(nbv[2 * qq], nbv[2 * qq + 1]),
@@ -336,7 +340,7 @@ __device__ __forceinline__ void adj_active(const Adj &A, const AdjRec &rec, Node
         f2 nb0 = mk(0.f, 0.f), nb1 = mk(0.f, 0.f);
         float rb = 0.f;
         capsule_vjp(Cw, n0, n1, w0, w1, k0, k1, ch, xb0, xb1, nb0, nb1, rb);
-        atomicAdd(&A.drd[t0], (double)rb);
+        atomicAdd(drd_word(A, i, t0), (double)rb);
         out.ne = 2;
         out.t[0] = t0, out.v[0] = edge_out(A, e0, up0, nb0, prev && k0 == W_STD);
         out.t[1] = t1, out.v[1] = edge_out(A, e1, up1, nb1, prev && k1 == W_STD);
@@ -397,7 +401,7 @@ __global__ void k_adj_finish(Adj A, float *dz0) {
 __global__ __launch_bounds__(64) void k_adj_radii(Adj A, float *dr) {
     const int i = blockIdx.x;
     double v = 0.0;
-    for (int s = threadIdx.x; s <= A.eta; s += 64) v += A.drd[node_id(A, i, s)];
+    for (int s = threadIdx.x; s <= (A.drd_agents ? 0 : A.eta); s += 64) v += *drd_word(A, i, node_id(A, i, s));
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     if (threadIdx.x == 0) dr[i] = (float)v;
 }
@@ -537,7 +541,8 @@ struct Buffers {
     char *set[2];
     size_t set_bytes;
     float *g;                     // [N][2]
-    double *drd;                  // [N]
+    double *drd;                  // [N], or [p] with drd_agents
+    bool drd_agents;
     unsigned *arena_cursor;
     // What a segment's recompute captures, twice: segment c uses copy c & 1,
     // so that one segment is recomputed while the one after it is reversed.
@@ -564,6 +569,7 @@ size_t set_layout(const Shape &h, char *base, float **ub = nullptr, float **sums
     return R.used;
 }
 
+// (B.drd_agents is set by the caller)
 bool layout(Region &R, const Shape &h, Buffers &B) {
     B.cur.z = R.take<float>((size_t)h.N * 2);
     B.cur.l = R.take<unsigned char>((size_t)h.N);
@@ -581,7 +587,7 @@ bool layout(Region &R, const Shape &h, Buffers &B) {
     B.set[0] = R.take<char>(B.set_bytes);
     B.set[1] = R.take<char>(B.set_bytes);
     B.g = R.take<float>((size_t)h.N * 2);
-    B.drd = R.take<double>((size_t)h.N);
+    B.drd = R.take<double>((size_t)(B.drd_agents ? h.p : h.N));
     B.arena_cursor = R.take<unsigned>(1);
     bool ok = true;
     for (int b = 0; b < 2; ++b) {
@@ -735,7 +741,7 @@ twa_status run_once(twa_solver *s, const Shape &h, Buffers &B, const float *dL_d
     A.e_energy = P.e_energy, A.e_coll = P.e_coll, A.e_wall = P.e_wall;
     A.f_energy = P.f_energy, A.f_coll = P.f_coll, A.f_wall = P.f_wall;
     A.radii = P.radii, A.walls = P.walls, A.C = P.C;
-    A.g = B.g, A.dx0 = dL_dx0, A.dxT = dL_dxT, A.drd = B.drd;
+    A.g = B.g, A.dx0 = dL_dx0, A.dxT = dL_dxT, A.drd = B.drd, A.drd_agents = B.drd_agents;
     int in = 0; // the set holding dL/d(state after the step being reversed)
     {
         float *ub, *sums;
@@ -746,7 +752,7 @@ twa_status run_once(twa_solver *s, const Shape &h, Buffers &B, const float *dL_d
     }
     HIP_TRY(s, hipMemsetAsync(dL_dx0, 0, sizeof(float) * s->p * 2, st));
     HIP_TRY(s, hipMemsetAsync(dL_dxT, 0, sizeof(float) * s->p * 2, st));
-    HIP_TRY(s, hipMemsetAsync(B.drd, 0, sizeof(double) * h.N, st));
+    HIP_TRY(s, hipMemsetAsync(B.drd, 0, sizeof(double) * (B.drd_agents ? h.p : h.N), st));
     const unsigned nb_nodes = (unsigned)((h.N + 255) / 256), nb_small = (unsigned)((P.f_coll + 255) / 256);
     const unsigned nb_rec = 256; // blocks striding over the captured records
     const unsigned nb_clr = 64;  // blocks clearing a step's output sparsely
@@ -1072,40 +1078,47 @@ extern "C" twa_status twa_backward_noalloc(twa_solver *s, const float *dL_dz, fl
     if (!base) return fail(s, TWA_E_STATE, "twa_backward_noalloc: no scratch on the solver's device");
     const bool use_tape = tape_covers(s);
     const Shape h = shape_of(s, use_tape ? s->tape.interval : 0);
-    Region R;
-    R.base = static_cast<char *>(base);
-    R.cap = kScratchBytes;
-    Buffers B{};
-    if (!layout(R, h, B)) {
-        Region sz;
-        layout(sz, h, B);
-        return fail(s, TWA_E_NOMEM, "twa_backward_noalloc: the run needs more than the " +
-                                        std::to_string(kScratchBytes >> 20) + " MiB scratch (" +
-                                        std::to_string(sz.used >> 20) + " MiB before its records)");
-    }
-    // the rest of the scratch holds the records: the checkpoints' first, the
-    // two capture pools share what they leave (less an alignment pad)
-    const size_t left = R.cap - std::min(R.cap, ((R.used + 255) & ~(size_t)255) + 256);
-    B.arena_cap = (unsigned)std::min<size_t>(left / sizeof(AdjRec), 0xffffffffu);
-    B.arena = R.take<AdjRec>(B.arena_cap);
-    B.pools_follow = true;
-    const unsigned total = B.arena_cap;
-    if (!B.arena || B.arena_cap < 256)
-        return fail(s, TWA_E_NOMEM, "twa_backward_noalloc: no scratch left for the records");
-    const bool was = s->no_capture;
-    s->no_capture = true; // replay graphs already captured, capture none (that would allocate)
-    int outcome = kDone;
-    unsigned need = 0;
-    const twa_status st =
-        run_once(s, h, B, dL_dz, dL_dx0, dL_dxT, dL_dr, dL_dz0, &outcome, &need, nullptr, use_tape, nullptr);
-    s->no_capture = was;
-    if (st != TWA_OK) return st;
-    if (outcome == kArenaFull)
-        return fail(s, TWA_E_NOMEM, "twa_backward_noalloc: the scratch holds " + std::to_string(total) +
-                                        " records, the checkpoints need " + std::to_string(need));
-    if (outcome != kDone)
+    // with the radius sums per node, and where that is what does not fit, once
+    // more with one per agent
+    for (int agents = 0;; ++agents) {
+        Region R;
+        R.base = static_cast<char *>(base);
+        R.cap = kScratchBytes;
+        Buffers B{};
+        B.drd_agents = agents != 0;
+        if (!layout(R, h, B)) {
+            if (!agents) continue;
+            Region sz;
+            layout(sz, h, B);
+            return fail(s, TWA_E_NOMEM, "twa_backward_noalloc: the run needs more than the " +
+                                            std::to_string(kScratchBytes >> 20) + " MiB scratch (" +
+                                            std::to_string(sz.used >> 20) + " MiB before its records)");
+        }
+        // the rest of the scratch holds the records: the checkpoints' first, the
+        // two capture pools share what they leave (less an alignment pad)
+        const size_t left = R.cap - std::min(R.cap, ((R.used + 255) & ~(size_t)255) + 256);
+        B.arena_cap = (unsigned)std::min<size_t>(left / sizeof(AdjRec), 0xffffffffu);
+        B.arena = R.take<AdjRec>(B.arena_cap);
+        B.pools_follow = true;
+        const unsigned total = B.arena_cap;
+        if (!B.arena || B.arena_cap < 256) {
+            if (!agents) continue;
+            return fail(s, TWA_E_NOMEM, "twa_backward_noalloc: no scratch left for the records");
+        }
+        const bool was = s->no_capture;
+        s->no_capture = true; // replay graphs already captured, capture none (that would allocate)
+        int outcome = kDone;
+        unsigned need = 0;
+        const twa_status st =
+            run_once(s, h, B, dL_dz, dL_dx0, dL_dxT, dL_dr, dL_dz0, &outcome, &need, nullptr, use_tape, nullptr);
+        s->no_capture = was;
+        if (st != TWA_OK || outcome == kDone) return st;
+        if (!agents) continue;
+        if (outcome == kArenaFull)
+            return fail(s, TWA_E_NOMEM, "twa_backward_noalloc: the scratch holds " + std::to_string(total) +
+                                            " records, the checkpoints need " + std::to_string(need));
         return fail(s, TWA_E_NOMEM, "twa_backward_noalloc: the checkpoints leave " + std::to_string(B.pool_cap) +
                                         " records of scratch to each capture pool, a segment needs " +
                                         std::to_string(need));
-    return TWA_OK;
+    }
 }
