@@ -2,12 +2,13 @@
 
 Candidates are (lanes per workgroup, number of workgroups) of the
 persistent kernel, where instances are packed onto workgroups
-longest-first by the library, and (0, 1): one launch per phase of an
-iteration over all instances.  This driver times a few iterations of each
-candidate on the actual batch (HIP events, through the C ABI) and keeps
-the fastest.  Results are cached in a JSON file keyed
-by device name and a shape signature of the batch, so a repeated batch
-shape skips the search.
+longest-first by the library, and (0, 1): a group of workgroups per
+instance, or one launch per phase of an iteration over all instances,
+as the batch's form and sizes have it.  This driver times a few iterations
+of each candidate on the actual batch (HIP events, through the C ABI) and
+keeps the fastest.  Results are cached in a JSON file keyed by device name,
+a shape signature of the batch, its flags and the library itself (what a
+candidate stands for depends on both), so a repeated batch skips the search.
 """
 from __future__ import annotations
 
@@ -22,6 +23,13 @@ CACHE = os.environ.get("TWA_TUNE_CACHE", os.path.join(os.path.expanduser("~"), "
 def shape_signature(instances) -> str:
     key = sorted((i.p, i.eta, i.dim, i.n_walls) for i in instances)
     return hashlib.sha1(json.dumps(key).encode()).hexdigest()[:16]
+
+
+def cache_key(device: str, instances, flags: int, iters: int) -> str:
+    from paper_1311_4527_amd import twa
+    with open(twa.LIB_PATH, "rb") as f:
+        lib = hashlib.sha1(f.read()).hexdigest()[:16]
+    return f"{device}|{shape_signature(instances)}|flags {int(flags)}|{iters}|{lib}"
 
 
 def candidates(n: int) -> List[Tuple[int, int]]:
@@ -53,8 +61,7 @@ def tune(batch, iters: int = 20, use_cache: bool = True, log: Optional[list] = N
     Tuning advances the batch's instances; callers that need a fixed start
     should tune on a copy of the batch (same shapes) or reset the state."""
     import torch
-    dev = torch.cuda.get_device_name(0)
-    key = f"{dev}|{shape_signature(batch.instances)}|{iters}"
+    key = cache_key(torch.cuda.get_device_name(0), batch.instances, batch.flags, iters)
     cache = _load_cache() if use_cache else {}
     if key in cache:
         b, g = cache[key]

@@ -376,14 +376,15 @@ class _Borrowed(Solver):
 
 class Batch:
     """Many independent instances advanced together (twa_batch_create ...
-    twa_batch_destroy): by one persistent launch, or by one launch per phase
-    over all instances (twa_batch_config(0, 1))."""
+    twa_batch_destroy): by one persistent launch, or (twa_batch_config(0, 1))
+    by groups of workgroups or one launch per phase over all instances."""
 
     def __init__(self, instances, flags=0, stream: Optional[torch.cuda.Stream] = None, device="cuda"):
         lib = load_library()
         self.device = device
         self.stream = stream if stream is not None else torch.cuda.current_stream(device)
         self.instances = list(instances)
+        self.flags = int(flags)
         self._keep = []
         arr = (_Instance * len(self.instances))()
         for k, inst in enumerate(self.instances):
@@ -396,7 +397,7 @@ class Batch:
                                _ptr(t["xT"]), _ptr(t["walls"]), _ptr(t["C"]), _ptr(t["z0"]),
                                float(inst.rho0), float(inst.alpha))
         h = ct.c_void_p()
-        st = lib.twa_batch_create(len(self.instances), ct.cast(arr, ct.c_void_p), int(flags),
+        st = lib.twa_batch_create(len(self.instances), ct.cast(arr, ct.c_void_p), self.flags,
                                   ct.c_void_p(self.stream.cuda_stream), ct.byref(h))
         if st != TWA_OK:
             raise TWAError(st, "twa_batch_create failed")
@@ -425,7 +426,8 @@ class Batch:
 
     def twa_batch_config(self, block: int, groups: int):
         """block 256 / 512 / 1024 lanes with `groups` bins: the persistent
-        kernel; block 0: the phased form (groups ignored)."""
+        kernel; block 0 (groups ignored): a group of workgroups per instance,
+        or one launch per phase where that is the faster way."""
         self._check(load_library().twa_batch_config(self.h, int(block), int(groups)))
 
     def twa_batch_iterate(self, k: int):
