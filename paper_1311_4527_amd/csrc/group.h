@@ -779,6 +779,9 @@ __global__ __launch_bounds__(kGroupBatchBlock, 3) void kp_group(const Params *in
     if (!who[2]) return;
     const unsigned rank = __builtin_amdgcn_readfirstlane(who[0]), size = __builtin_amdgcn_readfirstlane(who[1]);
     Params P = load_struct(insts + inst);
+    // (every pointer that group_run uses: one that is left out still works, at the
+    // price above.  A field added to Params or GroupArgs belongs here if it is one.)
+    static_assert(sizeof(Params) == 520 && sizeof(GroupArgs) == 104, "see above");
     in_global(P.zr_prev, base, at), in_global(P.zr_cur, base, at), in_global(P.radii, base, at), in_global(P.walls, base, at), in_global(P.C, base, at);
     in_global(P.xfix, base, at), in_global(P.u_coll, base, at), in_global(P.u_wall, base, at), in_global(P.u_energy, base, at), in_global(P.u_fixed, base, at);
     in_global(P.bits_coll, base, at), in_global(P.bits_wall, base, at), in_global(P.chunk_coll, base, at), in_global(P.counters, base, at), in_global(P.stats, base, at);

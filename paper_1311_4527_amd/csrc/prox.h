@@ -30,14 +30,15 @@ namespace twa {
 TWA_HD float inv_sqrt(float x) { return 1.0f / sqrtf(x); }
 
 // Correctly rounded quotients and roots of operands far from the ends of the
-// exponent range, from an estimate within an ulp: the steps of the compiler's own
-// division and root without the scaling and the special cases around them, and
-// with one reciprocal for all quotients by the same d.  For |n| and d in
-// [2^-100, 2^80] with n / d in [2^-100, 2^100], and x in [2^-90, 2^90]: no step
-// over- or underflows, every remainder is exact, and the result is n / d and
-// sqrtf(x) to the last bit.  (The one exception: d of all ones and n a power of
-// two want the correctly rounded estimate.  v_rcp_f32 gives it: on the device,
-// every mantissa of d and of x, 10^10 quotients, none differs from n / d.)
+// exponent range, from an estimate within an ulp, by Markstein's iterations
+// (P. Markstein, Computation of elementary functions on the IBM RISC System/6000
+// processor, IBM J. Res. Dev. 34 (1990)): exact remainders by fused multiply-adds,
+// no scaling and no special cases, one reciprocal for all quotients by the same d.
+// For |n| and d in [2^-100, 2^80] with n / d in [2^-100, 2^100], and x in [2^-90,
+// 2^90]: no step over- or underflows, every remainder is exact, and the result is
+// n / d and sqrtf(x) to the last bit.  (The one exception: d of all ones and n a power of
+// two want the correctly rounded estimate.  v_rcp_f32 gives it: a test compares
+// every significand of d and of x on the device.)
 TWA_HD float refined_rcp(float d, float r0) { return fmaf(fmaf(-d, r0, 1.f), r0, r0); }
 TWA_HD float quotient(float n, float d, float r) {
     float q = n * r;

@@ -2149,6 +2149,19 @@ __global__ void k_finite(const float4 *zr, long long N, const float *u, long lon
         if (!isfinite(u[q])) atomicOr(bad, 1);
 }
 
+// (tests) every significand of a divisor at this scale (a power of two), and of a
+// root's operand over two binades: mismatches of quotient() and root_of() with
+// the division and the root that the compiler makes
+__global__ void k_check_quotients(const float *num, int n, float scale, unsigned *bad) {
+    const unsigned m = blockIdx.x * blockDim.x + threadIdx.x; // 2^23 threads
+    const float d = __uint_as_float(0x3f800000u | m) * scale, r = rcp_of(d);
+    unsigned q = 0u, s = 0u;
+    for (int k = 0; k < n; ++k) q += __float_as_uint(quotient(num[k], d, r)) != __float_as_uint(num[k] / d);
+    for (int k = 1; k <= 2; ++k) s += __float_as_uint(root_of((float)k * d)) != __float_as_uint(sqrtf((float)k * d));
+    if (q) atomicAdd(&bad[0], q);
+    if (s) atomicAdd(&bad[1], s);
+}
+
 } // namespace
 
 // ============================================================================
@@ -3471,6 +3484,15 @@ twa_status twa_debug_group_stuck(twa_solver *s, int batch) {
     HIP_TRY(s, hipMemcpyAsync(const_cast<unsigned *>(at), &one, sizeof(one), hipMemcpyHostToDevice, s->stream));
     HIP_TRY(s, hipStreamSynchronize(s->stream));
     return TWA_OK;
+}
+
+// For the test of the minimisers' arithmetic on the device (not declared in the
+// header): num[n], bad[2] on the device.
+twa_status twa_debug_quotients(const float *num, int n, float scale, unsigned *bad, void *hip_stream) {
+    if (!num || n < 1 || !bad) return TWA_E_INVALID;
+    hipLaunchKernelGGL(k_check_quotients, dim3((1u << 23) / 256), dim3(256), 0, static_cast<hipStream_t>(hip_stream), num, n,
+                       scale, bad);
+    return hipGetLastError() == hipSuccess ? TWA_OK : TWA_E_DEVICE;
 }
 
 // For the tests of groups that start short (not declared in the header): later
