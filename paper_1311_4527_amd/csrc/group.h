@@ -25,9 +25,9 @@
 // every member has read it, and written again from iteration t + 3 on; so
 // one barrier per iteration is enough.
 //
-// Only workgroups that already run are ever waited for without a bound that a
-// working card meets.  They register; the first one waits for the rest (see
-// group_join) and then freezes the group at whoever came.  Later workgroups see
+// No barrier waits for a workgroup that does not run yet.  Workgroups register;
+// the first one waits for the rest, for a bounded time (see group_join), and
+// then freezes the group at whoever came.  Later workgroups see
 // the frozen mark and leave, the members share out all the shares.  No
 // assumption about residency or dispatch order is needed for progress or for
 // the result (fewer members are just slower).
