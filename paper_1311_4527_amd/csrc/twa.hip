@@ -3067,8 +3067,9 @@ static twa_status create_solver(int p, int eta, int dim, const float *radii, con
     // agents j).  Four rows a wave issue least, but a launch of few waves lasts as
     // long as one of them: fewer rows while that makes at most kWalkWaves waves
     // (525 agents, 14 intervals, 100 iterations: one row 2.28 ms, four 2.61; a
-    // training step of 5 agents 6.46 against 7.02).  Dense: chunks (i, j0) from j = i + 1 on, which are fewer than those
-    // cut at multiples of 64 (110 agents: 155 against 172).
+    // training step of 5 agents 6.46 against 7.02).  Dense: chunks (i, j0) from j = i +
+    // 1 on, which are fewer than those cut at multiples of 64 (110 agents: 155 against
+    // 172).
     const bool dense_walk = (flags & (TWA_F_DENSE | TWA_F_ADMM)) != 0;
     const long long blocks_s = (eta + P.cpw - 1) / P.cpw;
     std::vector<unsigned long long> hwalk;
